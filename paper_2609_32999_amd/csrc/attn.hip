@@ -8,7 +8,8 @@
 // up to and including p_t.
 //
 // Three kernels:
-//   attn_f32_kernel   fp32 reference mode, scalar, one workgroup per item.
+//   attn_f32_kernel   fp32 reference mode, fp64 MFMA, one workgroup per 16
+//                     rows and query head.
 //   attn_mfma_kernel  bf16 mode.  Work item = R row blocks of up to 32
 //                     rows of one request x one KV head (R = 1 or 3, chosen
 //                     per plan), consecutive in the plan's item row order
@@ -53,92 +54,206 @@ namespace {
 // The reference mode of the fp32 configurations: operands are fp32 (q_rot
 // and K rounded to fp32 like the storage), the arithmetic is fp64 (scores,
 // softmax statistics and the weighted sum of V), and the output is rounded
-// to fp32 once.  One workgroup per item, scalar code: its job is accuracy.
+// to fp32 once.
+//
+// Bound by latency: these batches are a few hundred rows (the tiny
+// configuration's whole launch is 20 MFLOP), so the work is cut for
+// parallelism.  A workgroup takes 16 rows of one query head; its waves take
+// the 16-key tiles of the rows' key range in turn, each with its own running
+// softmax, merged through LDS at the end.  Both products run on
+// v_mfma_f64_16x16x4_f64:
+//   S^T = K Q^T   lane l holds key l % 16 and row l % 16 over the D/4
+//                 consecutive dims of quarter l / 16 (the order of the
+//                 contraction is free, so a lane's dims are whole 16-byte
+//                 loads of its row);
+//   O^T += V^T P^T  result register r of S^T is key 4 r + l / 16 of the
+//                 tile, which is the operand layout of step r: P needs no
+//                 exchange.
+// 272 prompt tokens, 152 rows, 4 heads of 64: 1,176 us with scalar code, one
+// workgroup per 32 rows and KV head, rows one after another; 20 us so.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// Waves of a workgroup: eight, and four at head_dim 256, where a wave's
+// output tile alone is 128 registers.
+template <int D> constexpr int kF32Waves = D == 256 ? 4 : 8;
+constexpr int kF32Rows = 16, kF32Keys = 16;
+
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(
+__global__ __launch_bounds__(64 * kF32Waves<D>) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ kc,
     const float* __restrict__ vc, const AttnItem* __restrict__ items,
     const int32_t* __restrict__ bts, const RowDesc* __restrict__ rows,
     const float* __restrict__ rope_cos, const float* __restrict__ rope_sin,
     float* __restrict__ out, float* __restrict__ lse, int n_q_heads,
     int n_kv_heads, int log2_page, float scale) {
-  __shared__ float qs[D];
-  __shared__ double ps[256];
-  __shared__ double red[8];
+  constexpr int NW = kF32Waves<D>;
+  constexpr int DQ = D / 4;      // dims of a lane in S^T = K Q^T
+  constexpr int DT = D / 16;     // 16-dim blocks of the output
+  constexpr int kRound = 4;      // 16-dim blocks merged per round
+  __shared__ double om[NW][16 * kRound][kF32Rows];
+  __shared__ double ml[2][NW][kF32Rows];
   const AttnItem it = items[blockIdx.x];
-  if (it.n_rows == 0) return;
-  const int t = threadIdx.x;
+  const int r0 = kF32Rows * blockIdx.z;
+  if (r0 >= it.n_rows) return;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = tid & 15, c4 = (tid >> 4) & 3;
   const int G = n_q_heads / n_kv_heads;
   const int g = it.kv_head;
+  const int hq = g * G + blockIdx.y;
   const int page_mask = (1 << log2_page) - 1;
   const int32_t* bt = bts + it.bt_off;
+  // rows past the item's last one repeat it and store nothing
+  const int n_rows = min(kF32Rows, it.n_rows - r0);
+  const int row = it.row0 + r0 + min(c16, n_rows - 1);
+  const int pos = rows[row].pos;
+  // positions ascend
+  const int min_pos = rows[it.row0 + r0].pos;
+  const int kv_end = rows[it.row0 + r0 + n_rows - 1].pos + 1;
 
-  auto block_max = [&](double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    if ((t & 63) == 0) red[t >> 6] = v;
-    __syncthreads();
-    v = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-    __syncthreads();
-    return v;
-  };
-  auto block_sum = [&](double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if ((t & 63) == 0) red[4 + (t >> 6)] = v;
-    __syncthreads();
-    v = (red[4] + red[5]) + (red[6] + red[7]);
-    __syncthreads();
-    return v;
-  };
-  auto key_row = [&](const float* base, int k) {
-    const int page = bt[k >> log2_page];
-    return base + ((((int64_t)page * n_kv_heads + g) << log2_page) + (k & page_mask)) * D;
-  };
-  const double sc = scale;
-
-  for (int rr = 0; rr < it.n_rows; ++rr) {
-    const int row = it.row0 + rr;
-    const int pos = rows[row].pos;
-    for (int hh = 0; hh < G; ++hh) {
-      const int hq = g * G + hh;
-      const float* qp = q + ((int64_t)row * n_q_heads + hq) * D;
-      if (t < D / 2) {
-        float lo = qp[t], hi = qp[t + D / 2];
-        const float c = rope_cos[(int64_t)pos * (D / 2) + t];
-        const float s = rope_sin[(int64_t)pos * (D / 2) + t];
-        rope_rotate<1>(&lo, &hi, &c, &s);
-        qs[t] = lo;
-        qs[t + D / 2] = hi;
-      }
-      __syncthreads();
-      double m = -INFINITY, l = 0.0, o = 0.0;
-      for (int k0 = it.kv_lo; k0 <= pos; k0 += 256) {
-        const int k = k0 + t;
-        double s = -INFINITY;
-        if (k <= pos) {
-          const float* kp = key_row(kc, k);
-          double acc = 0.0;
-          for (int e = 0; e < D; ++e) acc = fma((double)qs[e], (double)kp[e], acc);
-          s = acc * sc;
-        }
-        const double mn = fmax(m, block_max(s));
-        const double p = (k <= pos) ? exp(s - mn) : 0.0;
-        ps[t] = p;
-        const double alpha = exp(m - mn);
-        l = l * alpha + block_sum(p);
-        if (t < D) {
-          const int nk = min(256, pos + 1 - k0);
-          double acc = 0.0;
-          for (int j = 0; j < nk; ++j) acc = fma(ps[j], (double)key_row(vc, k0 + j)[t], acc);
-          o = o * alpha + acc;
-        }
-        m = mn;
-        __syncthreads();
-      }
-      if (t < D) out[((int64_t)row * n_q_heads + hq) * D + t] = (float)(o / l);
-      if (t == 0 && lse) lse[(int64_t)row * n_q_heads + hq] = (float)(m + log(l));
-      __syncthreads();
+  // this lane's dims of the rotated query
+  float qr[DQ];
+  {
+    constexpr int H = D / 2;
+    const int d0 = DQ * c4, dl = d0 % H;   // first dim, and its index in a RoPE half
+    const float* qp = q + ((int64_t)row * n_q_heads + hq) * D + dl;
+    const float* cp = rope_cos + (int64_t)pos * H + dl;
+    const float* sp = rope_sin + (int64_t)pos * H + dl;
+#pragma unroll
+    for (int e = 0; e < DQ; e += 4) {
+      const float4 a = *reinterpret_cast<const float4*>(qp + e);
+      const float4 b = *reinterpret_cast<const float4*>(qp + H + e);
+      const float4 c = *reinterpret_cast<const float4*>(cp + e);
+      const float4 s = *reinterpret_cast<const float4*>(sp + e);
+      float lo[4] = {a.x, a.y, a.z, a.w}, hi[4] = {b.x, b.y, b.z, b.w};
+      const float cs[4] = {c.x, c.y, c.z, c.w}, sn[4] = {s.x, s.y, s.z, s.w};
+      rope_rotate<4>(lo, hi, cs, sn);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) qr[e + i] = d0 < H ? lo[i] : hi[i];
     }
   }
+
+  f64x4 o[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t) o[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double m = -INFINITY, l = 0.0;
+  const double sc = scale;
+  auto key_base = [&](int k) -> int64_t {   // keys past the range read its last one
+    const int kk = min(k, kv_end - 1);
+    return ((((int64_t)bt[kk >> log2_page] * n_kv_heads + g) << log2_page) + (kk & page_mask)) * D;
+  };
+  for (int k0 = it.kv_lo + kF32Keys * w; k0 < kv_end; k0 += kF32Keys * NW) {
+    const float* kp = kc + key_base(k0 + c16) + DQ * c4;
+    float4 kr[DQ / 4];
+#pragma unroll
+    for (int e = 0; e < DQ / 4; ++e) kr[e] = *reinterpret_cast<const float4*>(kp + 4 * e);
+    const float* vp[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) vp[r] = vc + key_base(k0 + 4 * r + c4) + c16;
+    f64x4 s = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < DQ / 4; ++e) {
+      s = __builtin_amdgcn_mfma_f64_16x16x4f64(kr[e].x, qr[4 * e], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f64_16x16x4f64(kr[e].y, qr[4 * e + 1], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f64_16x16x4f64(kr[e].z, qr[4 * e + 2], s, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f64_16x16x4f64(kr[e].w, qr[4 * e + 3], s, 0, 0, 0);
+    }
+    // register r of row c16: key k0 + 4 r + c4
+    double mt = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = k0 + 4 * r + c4 <= pos ? s[r] * sc : -INFINITY;
+      mt = fmax(mt, s[r]);
+    }
+    mt = fmax(mt, __shfl_xor(mt, 16));
+    mt = fmax(mt, __shfl_xor(mt, 32));
+    const double mn = fmax(m, mt);
+    // a row that sees no key of the wave's tiles yet keeps m at -inf
+    const double mb = mn == -INFINITY ? 0.0 : mn;
+    const double alpha = exp(m - mb);
+    m = mn;
+    double p[4], ps = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      p[r] = exp(s[r] - mb);
+      ps += p[r];
+    }
+    l = l * alpha + ps;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[t][i] *= alpha;
+    // A row must not meet the V of keys past its own: they weigh 0, but
+    // 0 x inf is not 0.  Only tiles past the block's smallest position hold
+    // such keys; if a V there is not finite, each row sums its own keys.
+    bool plain = true;
+    if (k0 + kF32Keys - 1 > min_pos) {
+      float z = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (k0 + 4 * r + c4 < kv_end)
+#pragma unroll
+          for (int t = 0; t < DT; ++t) z = fmaf(vp[r][16 * t], 0.0f, z);
+      plain = __builtin_amdgcn_ballot_w64(z != 0.0f) == 0;
+    }
+    if (plain) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool in = k0 + 4 * r + c4 < kv_end;
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+          o[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)vp[r][16 * t] : 0.0, p[r],
+                                                      o[t], 0, 0, 0);
+      }
+    } else {
+#pragma unroll 1
+      for (int j = 0; j < kF32Keys; ++j) {
+        const double pr = j < 8 ? (j < 4 ? p[0] : p[1]) : (j < 12 ? p[2] : p[3]);
+        const double pj = __shfl(pr, 16 * (j % 4) + c16);
+        if (k0 + j > pos) continue;
+        const float* vj = vc + key_base(k0 + j) + c4;
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[t][i] = fma(pj, (double)vj[16 * t + 4 * i], o[t][i]);
+      }
+    }
+  }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+
+  // merge the waves: weights exp(m_w - M), M the row's maximum (every row
+  // sees a key, so M is finite)
+  if (c4 == 0) {
+    ml[0][w][c16] = m;
+    ml[1][w][c16] = l;
+  }
+  __syncthreads();
+  double M = -INFINITY, L = 0.0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) M = fmax(M, ml[0][i][c16]);
+#pragma unroll
+  for (int i = 0; i < NW; ++i) L += ml[1][i][c16] * exp(ml[0][i][c16] - M);
+  const double wt = exp(m - M) / L;
+  for (int t0 = 0; t0 < DT; t0 += kRound) {
+    if (t0) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+      if (t / kRound * kRound == t0)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) om[w][16 * (t - t0) + 4 * r + c4][c16] = o[t][r] * wt;
+    __syncthreads();
+    for (int i = tid; i < 16 * kRound * kF32Rows; i += 64 * NW) {
+      const int d = i % (16 * kRound), r = i / (16 * kRound);
+      double a = 0.0;
+#pragma unroll
+      for (int x = 0; x < NW; ++x) a += om[x][d][r];
+      if (r < n_rows)
+        out[((int64_t)(it.row0 + r0 + r) * n_q_heads + hq) * D + 16 * t0 + d] = (float)a;
+    }
+  }
+  if (lse && w == 0 && c4 == 0 && c16 < n_rows)
+    lse[(int64_t)row * n_q_heads + hq] = (float)(M + log(L));
 }
 
 // ------------------------------------------------------------- bf16 mode
@@ -734,9 +849,9 @@ hipError_t launch_attn(const tsr_plan* p, int32_t part, const AttnItem* items,
   const int G = m.n_q_heads / m.n_kv_heads;
   const dim3 grid(n_items);
   if (m.act_dtype == TSR_F32) {
-    const dim3 block(256);
 #define TSR_F32K(DIM)                                                             \
-  hipLaunchKernelGGL(attn_f32_kernel<DIM>, grid, block, 0, s,                     \
+  hipLaunchKernelGGL(attn_f32_kernel<DIM>, dim3(n_items, G, kTileRows / kF32Rows), \
+                     dim3(64 * kF32Waves<DIM>), 0, s,                             \
                      static_cast<const float*>(q), static_cast<const float*>(req_k), \
                      static_cast<const float*>(req_v), items,                       \
                      p->dev.block_tables, p->dev.rows, p->dev.rope_cos,            \
