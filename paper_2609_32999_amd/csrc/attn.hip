@@ -50,6 +50,8 @@ namespace tsr {
 
 namespace {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // ------------------------------------------------------------- fp32 mode
 // The reference mode of the fp32 configurations: operands are fp32 (q_rot
 // and K rounded to fp32 like the storage), the arithmetic is fp64 (scores,
@@ -259,18 +261,16 @@ __global__ __launch_bounds__(64 * kF32Waves<D>) void attn_f32_kernel(
 // ------------------------------------------------------------- bf16 mode
 __device__ __forceinline__ uint32_t pack_f16x2(float a, float b) {
   // bf16 values convert to fp16 exactly inside fp16's normal range (the
-  // largest bf16 below fp16's maximum is 65280); the staging code refuses
-  // larger magnitudes, which this conversion (toward zero) would clip.
-  // (Round-to-nearest-even conversion, which would turn them infinite by
-  // itself, made the attention 10 % slower: it sits on the staging waves'
-  // path to every tile's barrier.)
-  const auto h = __builtin_amdgcn_cvt_pkrtz(a, b);
+  // largest bf16 below fp16's maximum is 65280); a larger one becomes
+  // infinite, so outputs that read it are non-finite instead of clipped.
+  const f16x2 h = {(_Float16)a, (_Float16)b};
   return __builtin_bit_cast(uint32_t, h);
 }
-// fp16 NaN pair: written over a thread's staged V^T values when one of
-// them is beyond fp16's range, so outputs that read them are non-finite
-// instead of silently clipped.
-constexpr uint32_t kF16NaN2 = 0x7E007E00u;
+// A K tile in LDS: for each 16-key block, four 1 KB blocks of 32 dims, in
+// which 8-dim chunk c of key k lies at 256 c + 16 k.  Fragment reads are
+// 256-byte runs at immediate offsets, and a direct load of 16 bytes a lane
+// by a wave that reads one page fills a 1 KB block.
+constexpr int kKHalf = 4 * kKBlk;
 
 // Masking of a tile's scores (tile loops are instantiated per kind).
 constexpr int kNoMask = 0, kMaskCausal = 1, kMaskBoth = 2;
@@ -378,132 +378,134 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
   float m = -INFINITY, l = 0.0f;
 
   // ---- staging.  A tile's 32 keys form two 16-key blocks; with B >= 16
-  // each block lies in one page.
-  // K: wave w loads fragment blocks kst = 2w, 2w + 1 with direct loads; lane
-  //    l fetches key l % 32, in 16-key block (l / 16) % 2.
-  // V: thread t owns 16 bytes (dims 8 (t / 16) ..) of keys 2 (t % 16) and
-  //    2 (t % 16) + 1, which sit next to each other in the permuted V^T row;
+  // each block lies in one page.  Staging wave w takes block w / 2 and 64 of
+  // its dims, so that a wave's page, and with it the base of its loads, is
+  // uniform: scalar address arithmetic, one 32-bit offset a lane, and no
+  // more than that held across a tile.
+  // (With a wave over both blocks, per-lane bases and a range check on V the
+  // kernel held 13 registers too many; RAG-8B 560 -> 532 us, its LOCAL form
+  // 232 -> 216, Long-70B 8.97 -> 8.52 ms.)  A tile's raw V lives in vectors
+  // local to one pass of the tile loop: as variables of the whole kernel it
+  // was split into scalars and copied right after the loads, which waits for
+  // them before the tile's products (10-15 % slower).
+  // K: direct loads; lane l fetches key l % 16, 8-dim chunk l / 16 of 32
+  //    dims, into its place in the fragment order (attn_common.h's order,
+  //    a 16-key block at a time).
+  // V: lane l owns 16 bytes (dims 8 (l / 8) ..) of keys 2 (l % 8) and
+  //    2 (l % 8) + 1, which sit next to each other in the permuted V^T row;
   //    each of its 8 dims takes one 4-byte write.
-  const int klane = (lane & 15) * kD + 8 * lh + 32 * w;
-  const bool khi = (lane >> 4) & 1;
-  uint4 vr[2];
-  const int kp = tid & 15;                 // key pair
-  const int vb = kp >> 3;                  // 16-key block of the pair
-  const int vc8 = (tid >> 4) * 8;          // first dim
-  const int voff = (2 * kp - 16 * vb) * kD + vc8;
-  const int vk = 2 * kp - 16 * vb;         // key within its block
-  const int vcol = 16 * vb + ((vk >> 2) & 1) * 8 + ((vk >> 3) & 1) * 4 + (vk & 3);
-  // Page ids of a tile's two 16-key blocks: uniform, so scalar loads, one
-  // tile before the tile's loads need them.
-  auto fetch_pages = [&](int j, int& q0, int& q1) __attribute__((always_inline)) {
-    q0 = bt[min((j * kKT) >> log2_page, it.n_pages - 1)];
-    q1 = bt[min((j * kKT + 16) >> log2_page, it.n_pages - 1)];
+  const int sb = w >> 1;                   // 16-key block
+  const uint32_t koff = ((lane & 15) * kD + 8 * (lane >> 4) + 64 * (w & 1)) * 2;
+  const int kp = lane & 7;                 // key pair within the block
+  const int vc8 = 64 * (w & 1) + 8 * (lane >> 3);   // first dim
+  const uint32_t voff = (2 * kp * kD + vc8) * 2;
+  const int vst = vc8 * kVStr + vt_col(16 * sb + 2 * kp);   // V^T element written
+  // The pages of the wave's block of a tile (K, and V where it may differ):
+  // uniform, so scalar loads, one tile before the tile's loads need them.
+  auto fetch_pages = [&](int j, int& pk, int& pv) __attribute__((always_inline)) {
+    const int i = min((j * kKT + 16 * sb) >> log2_page, it.n_pages - 1);
+    pk = bt[i];
+    if constexpr (AV || AK) pv = (AV ? vbts : bts)[it.bt_off + i];
   };
   auto block_base = [&](int page, int kq) -> int64_t {
     return ((((int64_t)page * n_kv_heads + g) << log2_page) + (kq & page_mask)) * kD;
   };
+  auto load16 = [](const uint16_t* base, uint32_t off) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(base) + off);
+  };
   // Issues tile j's loads: K directly into the LDS buffer kt, V into
   // registers (written to LDS as V^T by store_tile).
-  // K rotated on load: the staging thread's key (kk) and 8-dim chunk of each
-  // RoPE half, its raw K, and whether its block is a pool page
-  const int kk = tid & 31, kch = (tid >> 5) & 7;
-  uint4 kraw[2];
-  bool krot = false, kreg = false;
-  auto load_tile = [&](int j, int p0, int p1, uint8_t* kt) __attribute__((always_inline)) {
+  // K rotated on load: the lane's raw K of chunk kch of each RoPE half of
+  // key kk, and whether the wave's block is a pool page
+  const int kk = 16 * sb + (lane & 15), kch = (lane >> 4) + 4 * (w & 1);
+  u32x4 kraw[2];
+  bool krot = false;
+  auto load_tile = [&](int j, int pk, int pv, uint8_t* kt, u32x4& v0, u32x4& v1)
+      __attribute__((always_inline)) {
     const int key0 = j * kKT;
-    const int64_t b0 = block_base(p0 & ~kPoolPageFlag, key0);
-    const int64_t b1 = block_base(p1 & ~kPoolPageFlag, key0 + 16);
-    int64_t vbase = vb ? b1 : b0;
+    const int kb0 = key0 + 16 * sb;
+    const int64_t kbase = block_base(pk & ~kPoolPageFlag, kb0);
     const uint16_t* vsrc = vc;
+    int64_t vbase = kbase;
     if constexpr (AV || AK) {
-      // the V page: from the V block table (flagged pool pages) with V
-      // aliasing, else the request page of the unflagged block table
-      const int kv = key0 + 16 * vb;
-      const int32_t vp = (AV ? vbts : bts)[it.bt_off + min(kv >> log2_page, it.n_pages - 1)];
-      vsrc = (AV && (vp & kPoolPageFlag)) ? pool_v : vc;
-      vbase = block_base(vp & ~kPoolPageFlag, kv);
+      if (AV && (pv & kPoolPageFlag)) vsrc = pool_v;
+      vbase = block_base(pv & ~kPoolPageFlag, kb0);
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      vr[i] = *reinterpret_cast<const uint4*>(vsrc + vbase + voff + i * kD);
+    uint32_t o0 = voff, o1 = voff + kD * 2;
     if (key0 + kKT > it.kv_len) {
-      // last, partial tile: keys past kv_len may be unwritten slots.  Their
-      // scores are masked (a select), but 0 * NaN in P V would not be, so
-      // V is zeroed.
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if (key0 + 2 * kp + i >= it.kv_len) vr[i] = make_uint4(0, 0, 0, 0);
+      // Last, partial tile: keys past kv_len may be unwritten slots.  Their
+      // scores are masked (a select), but 0 * NaN in P V would not be, so a
+      // key of the tile stands in for them: the block's first, or the
+      // tile's where the whole block lies past kv_len.  (Addresses are
+      // replaced, not the loaded values: a select on those made tiles wait
+      // for their loads here, before their products.)
+      if (kb0 + 2 * kp >= it.kv_len) o0 = vc8 * 2;
+      if (kb0 + 2 * kp + 1 >= it.kv_len) o1 = vc8 * 2;
+      if (kb0 >= it.kv_len) {
+        const int i = key0 >> log2_page;
+        const int p0 = (AV ? vbts : bts)[it.bt_off + i];
+        vsrc = (AV && (p0 & kPoolPageFlag)) ? pool_v : vc;
+        vbase = block_base(p0 & ~kPoolPageFlag, key0);
+      }
     }
+    v0 = load16(vsrc + vbase, o0);
+    v1 = load16(vsrc + vbase, o1);
     if constexpr (AK) {
-      kreg = ((p0 | p1) & kPoolPageFlag) != 0;
-      if (kreg) {
-        // through registers: rotated (pool block) or copied (request block)
-        // by store_tile
-        const int kb = kk >> 4;
-        const int pg = kb ? p1 : p0;
-        krot = (pg & kPoolPageFlag) != 0;
-        const uint16_t* src = (krot ? pool_k : kc) +
-                              block_base(pg & ~kPoolPageFlag, key0 + kk) + 8 * kch;
-        kraw[0] = *reinterpret_cast<const uint4*>(src);
-        kraw[1] = *reinterpret_cast<const uint4*>(src + kD / 2);
+      krot = (pk & kPoolPageFlag) != 0;
+      if (krot) {   // through registers, rotated by store_k
+        const uint16_t* src = pool_k + kbase;
+        const uint32_t ko = ((lane & 15) * kD + 8 * kch) * 2;
+        kraw[0] = load16(src, ko);
+        kraw[1] = load16(src, ko + kD);
         return;
       }
     }
-    const uint16_t* ksrc = kc + (khi ? b1 : b0) + klane;
-    const uint32_t kdst = lds_addr(kt) + 2 * w * kKBlk;
-    lds_dma16(ksrc, kdst);
-    lds_dma16(ksrc + 16, kdst + kKBlk);
+    const uint32_t kdst = lds_addr(kt) + sb * kKHalf + (w & 1) * 2 * kKBlk;
+    lds_dma16<0>(kc + kbase, koff, kdst);
+    lds_dma16<64>(kc + kbase, koff, kdst + kKBlk);
   };
-  // K through registers (rotated on load): to LDS in fragment order, block
-  // kst holding dims 16 kst .. (lane l: key l % 32, dims + 8 (l / 32))
+  // K rotated on load: to LDS in fragment order
   auto store_k = [&](int j, uint8_t* kt) __attribute__((always_inline)) {
-    float lo[8], hi[8];
-    const uint32_t wl[4] = {kraw[0].x, kraw[0].y, kraw[0].z, kraw[0].w};
-    const uint32_t wh[4] = {kraw[1].x, kraw[1].y, kraw[1].z, kraw[1].w};
+    float lo[8], hi[8], c[8], sn[8];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      lo[2 * e] = bf16_to_f32(wl[e] & 0xffffu);
-      lo[2 * e + 1] = bf16_to_f32(wl[e] >> 16);
-      hi[2 * e] = bf16_to_f32(wh[e] & 0xffffu);
-      hi[2 * e + 1] = bf16_to_f32(wh[e] >> 16);
+      lo[2 * e] = bf16_to_f32(kraw[0][e] & 0xffffu);
+      lo[2 * e + 1] = bf16_to_f32(kraw[0][e] >> 16);
+      hi[2 * e] = bf16_to_f32(kraw[1][e] & 0xffffu);
+      hi[2 * e + 1] = bf16_to_f32(kraw[1][e] >> 16);
     }
-    uint4 a = kraw[0], b = kraw[1];
-    if (krot) {
-      const int pk = j * kKT + kk;
-      float c[8], sn[8];
-      load8(rope_cos + (int64_t)pk * (kD / 2) + 8 * kch, c);
-      load8(rope_sin + (int64_t)pk * (kD / 2) + 8 * kch, sn);
-      rope_rotate<8>(lo, hi, c, sn);
-      a.x = f32_to_bf16(lo[0]) | (f32_to_bf16(lo[1]) << 16);
-      a.y = f32_to_bf16(lo[2]) | (f32_to_bf16(lo[3]) << 16);
-      a.z = f32_to_bf16(lo[4]) | (f32_to_bf16(lo[5]) << 16);
-      a.w = f32_to_bf16(lo[6]) | (f32_to_bf16(lo[7]) << 16);
-      b.x = f32_to_bf16(hi[0]) | (f32_to_bf16(hi[1]) << 16);
-      b.y = f32_to_bf16(hi[2]) | (f32_to_bf16(hi[3]) << 16);
-      b.z = f32_to_bf16(hi[4]) | (f32_to_bf16(hi[5]) << 16);
-      b.w = f32_to_bf16(hi[6]) | (f32_to_bf16(hi[7]) << 16);
-    }
-    const int lofs = (kk + 32 * (kch & 1)) * 16;
-    *reinterpret_cast<uint4*>(kt + (kch >> 1) * kKBlk + lofs) = a;
-    *reinterpret_cast<uint4*>(kt + (4 + (kch >> 1)) * kKBlk + lofs) = b;
+    const int pk = j * kKT + kk;
+    load8(rope_cos + (int64_t)pk * (kD / 2) + 8 * kch, c);
+    load8(rope_sin + (int64_t)pk * (kD / 2) + 8 * kch, sn);
+    rope_rotate<8>(lo, hi, c, sn);
+    uint4 a, b;
+    a.x = f32_to_bf16(lo[0]) | (f32_to_bf16(lo[1]) << 16);
+    a.y = f32_to_bf16(lo[2]) | (f32_to_bf16(lo[3]) << 16);
+    a.z = f32_to_bf16(lo[4]) | (f32_to_bf16(lo[5]) << 16);
+    a.w = f32_to_bf16(lo[6]) | (f32_to_bf16(lo[7]) << 16);
+    b.x = f32_to_bf16(hi[0]) | (f32_to_bf16(hi[1]) << 16);
+    b.y = f32_to_bf16(hi[2]) | (f32_to_bf16(hi[3]) << 16);
+    b.z = f32_to_bf16(hi[4]) | (f32_to_bf16(hi[5]) << 16);
+    b.w = f32_to_bf16(hi[6]) | (f32_to_bf16(hi[7]) << 16);
+    uint8_t* dst = kt + sb * kKHalf + (kch >> 2) * kKBlk + (kch & 3) * 256 + (lane & 15) * 16;
+    *reinterpret_cast<uint4*>(dst) = a;
+    *reinterpret_cast<uint4*>(dst + 2 * kKBlk) = b;
   };
-  auto store_tile = [&](uint16_t* vs) __attribute__((always_inline)) {
-    const uint32_t* v0 = reinterpret_cast<const uint32_t*>(&vr[0]);
-    const uint32_t* v1 = reinterpret_cast<const uint32_t*>(&vr[1]);
-    float vmax = 0.0f;
+  auto store_tile = [&](const u32x4& v0, const u32x4& v1, uint16_t* vs)
+      __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int sh = (e & 1) ? 16 : 0;
-      const float f0 = bf16_to_f32((v0[e >> 1] >> sh) & 0xffffu);
-      const float f1 = bf16_to_f32((v1[e >> 1] >> sh) & 0xffffu);
-      vmax = fmaxf(vmax, fmaxf(fabsf(f0), fabsf(f1)));
-      *reinterpret_cast<uint32_t*>(vs + (vc8 + e) * kVStr + vcol) = pack_f16x2(f0, f1);
+      const float f0 = e & 1 ? __uint_as_float(v0[e >> 1] & 0xffff0000u)
+                             : __uint_as_float(v0[e >> 1] << 16);
+      const float f1 = e & 1 ? __uint_as_float(v1[e >> 1] & 0xffff0000u)
+                             : __uint_as_float(v1[e >> 1] << 16);
+      *reinterpret_cast<uint32_t*>(vs + vst + e * kVStr) = pack_f16x2(f0, f1);
     }
-    if (!(vmax <= 65280.0f)) {   // beyond fp16 (or NaN): refuse loudly
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        *reinterpret_cast<uint32_t*>(vs + (vc8 + e) * kVStr + vcol) = kF16NaN2;
-    }
+  };
+  // K fragment kst: the lane's key l % 32, dims 16 kst + 8 (l / 32) ..
+  const int kfl = ((lane >> 4) & 1) * kKHalf + (lane >> 5) * 256 + (lane & 15) * 16;
+  auto kfrag = [&](const uint8_t* ks, int kst) __attribute__((always_inline)) {
+    return *reinterpret_cast<const uint4*>(ks + kfl + (kst >> 1) * kKBlk + (kst & 1) * 512);
   };
 
   // One 32-key tile: S^T = K Q^T, online softmax, O^T += V^T P^T.
@@ -519,7 +521,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
 #pragma unroll
     for (int kst = 0; kst < 8; ++kst) {
       Frag a;
-      a.u = *reinterpret_cast<const uint4*>(ks + kst * kKBlk + lane * 16);
+      a.u = kfrag(ks, kst);
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.b, qfrag(kst), s, 0, 0, 0);
     }
     // keep four LDS fragment reads in flight ahead of the MFMAs
@@ -569,7 +571,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
 #pragma unroll
       for (int kst = 0; kst < 8; ++kst) {
         Frag a;
-        a.u = *reinterpret_cast<const uint4*>(ks + kst * kKBlk + lane * 16);
+        a.u = kfrag(ks, kst);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.b, qfrag(kst), s, 0, 0, 0);
       }
       if constexpr (MASK != kNoMask) {
@@ -627,7 +629,8 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
   const int nfull = min(ntiles, (it.min_pos + 1) / kKT);      // tiles ending at or before min_pos
   // page ids of the next tile to load (staging waves; the first tile's
   // come with the item)
-  int pp0 = it.pg[0], pp1 = it.pg[1];
+  int pp0 = sb ? it.pg[1] : it.pg[0], pp1 = 0;
+  if (AV || AK) fetch_pages(j0, pp0, pp1);
   // One tile j: issue the next tile's loads into the other buffers, compute
   // this one, stage the next V^T, wait for this wave's direct K loads, then
   // the workgroup barrier.
@@ -637,14 +640,15 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
     constexpr bool SKIP = R > 1 && decltype(skip_tag)::value;
     for (int j = ja; j < jb; ++j) {
       const bool more = j + 1 < ntiles;
+      u32x4 v0, v1;
       if (more) {
-        load_tile(j + 1, pp0, pp1, kl[(j + 1) & 1]);
+        load_tile(j + 1, pp0, pp1, kl[(j + 1) & 1], v0, v1);
         fetch_pages(j + 2, pp0, pp1);
       }
       if (!SKIP || j < my_ntiles) tile(j, mask_tag, kl[j & 1], vl[j & 1]);
       if (more) {
-        store_tile(vl[(j + 1) & 1]);
-        if (AK && kreg) store_k(j + 1, kl[(j + 1) & 1]);
+        store_tile(v0, v1, vl[(j + 1) & 1]);
+        if (AK && krot) store_k(j + 1, kl[(j + 1) & 1]);
       }
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
@@ -661,8 +665,9 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
       __syncthreads();
     }
   };
+  u32x4 vf0, vf1;
   if (stager) {
-    load_tile(j0, pp0, pp1, kl[j0 & 1]);
+    load_tile(j0, pp0, pp1, kl[j0 & 1], vf0, vf1);
     fetch_pages(j0 + 1, pp0, pp1);
   }
   // While the first tile is in flight: each row block's cos/sin rows go to
@@ -689,8 +694,8 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
     }
   }
   if (stager) {
-    store_tile(vl[j0 & 1]);
-    if (AK && kreg) store_k(j0, kl[j0 & 1]);
+    store_tile(vf0, vf1, vl[j0 & 1]);
+    if (AK && krot) store_k(j0, kl[j0 & 1]);
   }
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
   __syncthreads();

@@ -65,6 +65,14 @@ __device__ __forceinline__ void lds_dma16(const void* src, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(src), "s"(lds) : "m0");
 }
+// The same from a wave-uniform address plus a 32-bit lane offset in bytes
+// plus OFS: one address register a lane instead of two, no 64-bit adds.  The
+// instruction adds its offset to the LDS address too, hence the lds - OFS.
+template <int OFS>
+__device__ __forceinline__ void lds_dma16(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+               :: "v"(off), "s"(base), "s"(lds - OFS), "n"(OFS) : "m0");
+}
 #pragma clang diagnostic pop
 
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
