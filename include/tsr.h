@@ -224,7 +224,7 @@ tsr_status tsr_plan_create(const tsr_model* model, const tsr_request* reqs,
  *   split_tiles  key-range splitting of long attention items (plans of
  *             the bf16 row-block kernel; other plans ignore it).
  *             An item whose keys span more than S tiles of 32 keys runs as
- *             ceil(tiles / S) items over consecutive key ranges, each
+ *             ceil(tiles / S) items over consecutive equal key ranges, each
  *             writing its rows' normalized output and log-sum-exp in fp32
  *             to a buffer in the plan workspace; a second kernel on the
  *             same stream merges them (o = sum_c exp(lse_c - lse) o_c,
@@ -234,7 +234,8 @@ tsr_status tsr_plan_create(const tsr_model* model, const tsr_request* reqs,
  *             prompt while most rows attend within a short unit.
  *               0   automatic: for items of one row block, S = the
  *                   launch's mean key tiles per compute unit (256 units,
- *                   32 tiles at least), so only items that would outlast
+ *                   24 tiles at least), or 65 % of that in launches of
+ *                   fewer than 768 items, so only items that would outlast
  *                   the rest of the launch are split; items of three row
  *                   blocks are not split; never for tsr_plan_create_static;
  *               >0  S = split_tiles;

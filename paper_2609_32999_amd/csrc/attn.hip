@@ -565,7 +565,10 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
 #pragma unroll
     for (int r = 0; r < 4; ++r) ls[r] = (s[r] + s[r + 4]) + (s[r + 8] + s[r + 12]);
     float lt = (ls[0] + ls[1]) + (ls[2] + ls[3]);
-    if (__builtin_amdgcn_ballot_w64(!(lt <= kLazySum) || m == -INFINITY)) {
+    // A row that sees no key up to here (in a key range of a split item past
+    // its position) waits with m at -inf.
+    const bool sees = MASK != kMaskCausal || pos_l >= j * kKT;
+    if (__builtin_amdgcn_ballot_w64(!(lt <= kLazySum) || (m == -INFINITY && sees))) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.0f;
 #pragma unroll
@@ -747,11 +750,13 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
   // ---- epilogue: normalise, round to bf16, store rows of this tile
   const float lt = l + __shfl_xor(l, 32);
   if (!wave_active || rbase + lrow >= it.n_rows) return;
-  const float inv = 1.0f / lt;
+  float inv = 1.0f / lt;
   {
     if (it.part_slot >= 0) {
       // one key range of a split item: normalized rows and log-sum-exp in
-      // fp32 to this row block's slot, merged by attn_merge_kernel
+      // fp32 to this row block's slot, merged by attn_merge_kernel; a row
+      // that sees no key of the range weighs nothing there (0, -inf)
+      if (m == -INFINITY) inv = 0.0f;
       const int64_t slot = it.part_slot + (int64_t)rb * it.n_parts;
       const int64_t sr = (slot * kTileRows + lrow) * kSplitHeads + w;
       float* po = split_o + sr * kD;
@@ -762,7 +767,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
           *reinterpret_cast<float4*>(po + 32 * db + 8 * rg + 4 * lh) =
               make_float4(o[db][4 * rg] * inv, o[db][4 * rg + 1] * inv,
                           o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-      if (lh == 0) split_lse[sr] = m * scale + logf(lt);
+      if (lh == 0) split_lse[sr] = m == -INFINITY ? -INFINITY : m * scale + logf(lt);
       return;
     }
   }
@@ -791,55 +796,61 @@ int ilog2(int x) {
 // whole prompt, run as several ranges): for its row r and query head
 // hq0 + hs, from the ranges' normalized outputs o_c and log-sum-exps lse_c,
 //   lse = log sum_c exp(lse_c),   o = sum_c exp(lse_c - lse) o_c,
-// o rounded to bf16 once.  One workgroup per row block of a split item (its
-// rows are AttnRow entries), two threads per (row, head), each over half the
-// head dims.
-template <int D>
+// o rounded to bf16 once.
+//
+// Bound by reading the partial rows, which the split kernel has just left in
+// the caches.  Half a wave takes a (row, head): its 32 lanes read the 512
+// bytes of a partial row together and lane c % 32 holds the weight of range
+// c.  kMergeCut workgroups share a row block of a split item, so that a
+// launch of a few dozen row blocks still fills the chip.
+constexpr int kMergeCut = 8;
+constexpr int kMergePairs = kTileRows * kSplitHeads / kMergeCut;   // (row, head)s each
+
 __global__ __launch_bounds__(256) void attn_merge_kernel(
     const CombineDesc* __restrict__ cds, const AttnRow* __restrict__ arows,
     const float* __restrict__ split_o, const float* __restrict__ split_lse,
     uint16_t* __restrict__ out, float* __restrict__ lse, int n_q_heads) {
   const CombineDesc cd = cds[blockIdx.x];
-  const int t = threadIdx.x;
-  const int half = t & 1, pair = t >> 1;
-  const int r = pair / kSplitHeads, hs = pair % kSplitHeads;
-  if (r >= cd.n_rows || hs >= cd.n_heads) return;
-  auto slot_row = [&](int c) -> int64_t {
-    return ((int64_t)(cd.slot0 + c) * kTileRows + r) * kSplitHeads + hs;
-  };
-  float mx = -INFINITY;
-  for (int c = 0; c < cd.n_slots; ++c) mx = fmaxf(mx, split_lse[slot_row(c)]);
-  float den = 0.0f;
-  for (int c = 0; c < cd.n_slots; ++c) den += expf(split_lse[slot_row(c)] - mx);
-  const float ltot = mx + logf(den);
-  constexpr int DH = D / 2;
-  float acc[DH];
+  const int lane = threadIdx.x & 31;
+  for (int i = threadIdx.x >> 5; i < kMergePairs; i += 8) {
+    const int pair = blockIdx.y * kMergePairs + i;
+    const int r = pair / kSplitHeads, hs = pair % kSplitHeads;
+    if (r >= cd.n_rows || hs >= cd.n_heads) continue;
+    auto slot_row = [&](int c) -> int64_t {
+      return ((int64_t)(cd.slot0 + c) * kTileRows + r) * kSplitHeads + hs;
+    };
+    auto range_lse = [&](int c) { return c < cd.n_slots ? split_lse[slot_row(c)] : -INFINITY; };
+    float mx = -INFINITY;
+    for (int c = lane; c < cd.n_slots; c += 32) mx = fmaxf(mx, range_lse(c));
 #pragma unroll
-  for (int d = 0; d < DH; ++d) acc[d] = 0.0f;
-  for (int c = 0; c < cd.n_slots; ++c) {
-    const float wc = expf(split_lse[slot_row(c)] - ltot);
-    const float* src = split_o + slot_row(c) * D + half * DH;
+    for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    float den = 0.0f;
+    for (int c = lane; c < cd.n_slots; c += 32) den += expf(range_lse(c) - mx);
 #pragma unroll
-    for (int d = 0; d < DH; d += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(src + d);
-      acc[d] = fmaf(wc, v.x, acc[d]);
-      acc[d + 1] = fmaf(wc, v.y, acc[d + 1]);
-      acc[d + 2] = fmaf(wc, v.z, acc[d + 2]);
-      acc[d + 3] = fmaf(wc, v.w, acc[d + 3]);
+    for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
+    const float ltot = mx + logf(den);
+    float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int c0 = 0; c0 < cd.n_slots; c0 += 32) {
+      const int nc = min(32, cd.n_slots - c0);
+      const float wl = expf(range_lse(c0 + lane) - ltot);
+#pragma unroll 4
+      for (int c = 0; c < nc; ++c) {
+        const float wc = __shfl(wl, c, 32);
+        const float4 v =
+            *reinterpret_cast<const float4*>(split_o + slot_row(c0 + c) * kD + 4 * lane);
+        acc.x = fmaf(wc, v.x, acc.x);
+        acc.y = fmaf(wc, v.y, acc.y);
+        acc.z = fmaf(wc, v.z, acc.z);
+        acc.w = fmaf(wc, v.w, acc.w);
+      }
     }
+    const int64_t orow = (int64_t)arows[cd.row0 + r].row * n_q_heads + cd.hq0 + hs;
+    uint2 v;
+    v.x = f32_to_bf16(acc.x) | (f32_to_bf16(acc.y) << 16);
+    v.y = f32_to_bf16(acc.z) | (f32_to_bf16(acc.w) << 16);
+    *reinterpret_cast<uint2*>(out + orow * kD + 4 * lane) = v;
+    if (lse && lane == 0) lse[orow] = ltot;
   }
-  const int64_t orow = (int64_t)arows[cd.row0 + r].row * n_q_heads + cd.hq0 + hs;
-  uint16_t* dst = out + orow * D + half * DH;
-#pragma unroll
-  for (int d = 0; d < DH; d += 8) {
-    uint4 v;
-    v.x = f32_to_bf16(acc[d]) | (f32_to_bf16(acc[d + 1]) << 16);
-    v.y = f32_to_bf16(acc[d + 2]) | (f32_to_bf16(acc[d + 3]) << 16);
-    v.z = f32_to_bf16(acc[d + 4]) | (f32_to_bf16(acc[d + 5]) << 16);
-    v.w = f32_to_bf16(acc[d + 6]) | (f32_to_bf16(acc[d + 7]) << 16);
-    *reinterpret_cast<uint4*>(dst + d) = v;
-  }
-  if (lse && half == 0) lse[orow] = ltot;
 }
 
 }  // namespace
@@ -911,7 +922,8 @@ hipError_t launch_attn(const tsr_plan* p, int32_t part, const AttnItem* items,
   const int32_t c0 = part == TSR_ATTN_AFTER_COMPOSE ? p->n_combine_part[0] : 0;
   const int32_t nc = part == TSR_ATTN_ALL ? p->n_combine : p->n_combine_part[part - 1];
   if (nc == 0) return hipSuccess;
-  hipLaunchKernelGGL(attn_merge_kernel<kD>, dim3(nc), dim3(256), 0, s, p->dev.combine + c0,
+  hipLaunchKernelGGL(attn_merge_kernel, dim3(nc, kMergeCut), dim3(256), 0, s,
+                     p->dev.combine + c0,
                      p->dev.attn_rows, p->dev.split_o, p->dev.split_lse, static_cast<uint16_t*>(out), lse,
                      m.n_q_heads);
   return hipGetLastError();

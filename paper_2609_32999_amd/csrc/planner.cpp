@@ -456,9 +456,10 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   p->row_blocks = 1;
   const bool bf16_kv = m.act_dtype == TSR_BF16 && m.kv_dtype == TSR_BF16;
   auto split_threshold = [&](int64_t total_tiles) -> int64_t {
-    return split_tiles > 0 ? split_tiles
-                           : std::max<int64_t>(kMinSplitTiles,
-                                               (total_tiles + kSplitSlots - 1) / kSplitSlots);
+    if (split_tiles > 0) return split_tiles;
+    int64_t mean = (total_tiles + kSplitSlots - 1) / kSplitSlots;
+    if ((int64_t)items.size() < kFullLaunchItems) mean = mean * kSplitSharePct / 100;
+    return std::max<int64_t>(kMinSplitTiles, mean);
   };
   const bool mfma = m.act_dtype == TSR_BF16 &&
                     (m.kv_dtype == TSR_BF16 || m.kv_dtype == TSR_E4M3);
@@ -485,11 +486,11 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   for (int32_t i = 0; i < T; ++i) attn_rows[i] = AttnRow{ord[i], p->row_pos[ord[i]]};
   // Key-range split (bf16 plans of the row-block kernel): the launch
   // lasts as long as its longest item, so an item spanning more than S key
-  // tiles runs as up to n = ceil(tiles / S) items over consecutive key
-  // ranges.  Every range but the first starts on a tile boundary above
-  // kv_lo and at or below the smallest row position, so every row sees at
-  // least one key of every range and only the last range needs the causal
-  // mask; each range writes one split buffer slot per row block (a row
+  // tiles runs as n = ceil(tiles / S) items over consecutive, equal key
+  // ranges.  Every range but the first starts on a tile boundary.  A row past
+  // whose position a range starts sees none of its keys: the kernel gives it
+  // the weight 0 there (log-sum-exp -inf); the first range holds a key of
+  // every row.  Each range writes one split buffer slot per row block (a row
   // block's n ranges in consecutive slots) and the merge kernel combines
   // each row block's n slots.  Ranges inherit the item's part (a part-0
   // item's ranges read no gathered key either).
@@ -526,22 +527,15 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
       const int32_t j0 = a.kv_lo / kMfmaKeys;
       const int32_t ntl = (a.kv_len + kMfmaKeys - 1) / kMfmaKeys;
       const int64_t t = ntl - j0;
-      // interior boundaries: strictly increasing in (j0, top] with top the
-      // tile of the smallest row position, so that every range starts at a
-      // key every row sees (no row of a range is left without a visible
-      // key) and only the last range holds keys past a row's position
-      const int32_t top = std::min(ntl - 1, a.min_pos / kMfmaKeys);
-      const int64_t n = std::min<int64_t>((t + S - 1) / S, (int64_t)top - j0 + 1);
-      if (t <= S || n < 2) {
+      // equal ranges; a row past whose position a range lies sees none of
+      // its keys and weighs nothing there
+      const int64_t n = (t + S - 1) / S;
+      if (n < 2) {
         split.push_back(x);
         continue;
       }
       std::vector<int32_t> b((size_t)n + 1);
-      b[0] = j0;
-      b[n] = ntl;
-      for (int64_t c = 1; c < n; ++c)
-        b[c] = std::min<int32_t>(top - (int32_t)(n - 1 - c), j0 + (int32_t)((c * t + n / 2) / n));
-      for (int64_t c = 1; c < n; ++c) b[c] = std::max(b[c], b[c - 1] + 1);
+      for (int64_t c = 0; c <= n; ++c) b[c] = j0 + (int32_t)(c * t / n);
       for (int64_t c = 0; c < n; ++c) {
         Item y = x;
         y.it.kv_lo = c == 0 ? a.kv_lo : b[c] * kMfmaKeys;

@@ -143,12 +143,20 @@ struct alignas(16) CombineDesc {
 constexpr int kSplitHeads = 4;
 // The automatic key-range split caps items at the launch's mean key tiles
 // per compute unit (256 on MI355X): a longer item would outlast the launch
-// even with a compute unit to itself.  (Capping at the mean per workgroup
-// slot, three per unit, split the RAG-8B batch under the LOCAL scope into
-// 256 more items and did not shorten it: that launch is bound by its total
-// work, not by its longest item.)
+// even with a compute unit to itself.  A launch of fewer items than the chip
+// holds at once (three one-row-block workgroups a unit) has nothing left to
+// fill the units whose items end first, and is capped at kSplitSharePct per
+// cent of that: one RAG request (440 items, mean 142 tiles) ran 137 us capped
+// at its mean and 110 at anything from 84 to 112 tiles; below 80 the ranges'
+// partial rows cost more than they spread (119 us at 64, 131 at 24).  With
+// every chunk cached (64 items, mean 21) 24 tiles gave 37 us, 32 gave 40 and
+// 16 gave 38.  (Capping larger launches at the mean per workgroup slot did
+// not shorten the RAG-8B batch under the LOCAL scope: that launch is bound
+// by its total work, not by its longest item.)
 constexpr int kSplitSlots = 256;
-constexpr int kMinSplitTiles = 32;
+constexpr int kFullLaunchItems = 3 * kNumCus;
+constexpr int kSplitSharePct = 65;
+constexpr int kMinSplitTiles = 24;
 // At most this many split buffer slots (64 KiB each at head_dim 128).
 constexpr int kMaxSplitSlots = 4096;
 

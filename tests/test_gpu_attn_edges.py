@@ -36,3 +36,21 @@ def test_last_tile(last, kernel, page, alias_v):
     check_request(run, 0, check_kv=not alias_v)
     if not alias_v:
         check_request_sentinels(run, 0)
+
+
+@pytest.mark.parametrize("kernel", [3, 4])
+@pytest.mark.parametrize("split,over", [
+    (1, dict(unit_tokens=(250, 300), units_per_request=6, pool_units=8)),   # over 32 ranges
+    (2, {}),
+    (3, dict(n_recompute=1, instruction_tokens=0, query_tokens=1)),
+    (5, dict(n_requests=1)),
+])
+def test_split_ranges_past_rows(kernel, split, over):
+    """Every unit cached: an item's rows are recompute windows far apart, so
+    most key ranges lie past some of its rows, which weigh nothing there."""
+    wl = workloads.make_workload(workloads.get_config("small_bf16").with_(
+        hit_prob=1.0, residency_pattern=None, **over))
+    run = GpuRun(wl, attn_kernel=kernel, split_tiles=split)
+    assert run.plan.num_attn_splits > 0
+    for r in range(len(wl.requests)):
+        check_request(run, r)
