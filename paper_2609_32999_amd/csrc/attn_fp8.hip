@@ -18,6 +18,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "attn_common.h"
 #include "kernels_common.h"
 #include "tsr_internal.h"
 
@@ -25,30 +26,16 @@ namespace tsr {
 
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-union Frag8 {
-  uint4 u;
-  uint32_t w[4];
-  f16x8 h;
-};
-
-constexpr int kD = 128;
-// Keys per tile.  With 64 the kernel spilled about 40 registers inside the
-// tile loop; with 32 a wave holds 163 registers, three waves per SIMD.
-constexpr int kKT = 32;
-constexpr int kKStr = kD + 16;         // bytes per e4m3 K row in LDS
-// V^T rows (fp16) are 16-byte aligned and hold each 16-key step permuted as
-// keys [0..3, 8..11, 4..7, 12..15], so that the eight keys a lane feeds to
-// the PV MFMA are one 16-byte LDS read (as in the bf16 kernel).
-constexpr int kVStr = kKT + 8;         // fp16 elements per V^T row in LDS
-constexpr int kKBytes = kKT * kKStr;
+// An e4m3 K tile in LDS: for each 16-key block and 64-dim step kst a 1 KB
+// block in which 16-byte chunk c of key k lies at 256 c + 16 k.  One direct
+// load by a wave that reads one page fills a 1 KB block, and a fragment (32
+// bytes of a key) is two 16-byte reads in 256-byte runs.
+constexpr int kK8Blk = 1024;
+constexpr int kK8Bytes = 4 * kK8Blk;
 constexpr int kVElems = kD * kVStr;
-constexpr float kLazy = 8.0f;          // lazy-rescale threshold (log2 units)
-constexpr float kLazySum = 256.0f;     // 2^kLazy
 
 __device__ __forceinline__ int page_scale_exp(float amax) {
   if (!(amax > 0.0f)) return 0;
@@ -71,7 +58,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
     float* __restrict__ lse, int n_q_heads, int n_kv_heads, int log2_page,
     float scale_log2e) {
   constexpr int HPW = 1;  // query heads per wave
-  __shared__ __attribute__((aligned(16))) uint8_t kmem[2][kKBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t kmem[2][kK8Bytes];
   __shared__ __attribute__((aligned(16))) uint16_t vmem[2][kVElems];
   // K page scales of each staged tile's two 16-key blocks
   __shared__ float kscl[2][2];
@@ -96,13 +83,113 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
   const int rbase = 32 * rb;
   // item rows are entries of arows: the computed row (q, out, lse) and
   // its position (with three row blocks, each request's rows grouped by
-  // first visible key)
-  const AttnRow ar = arows[it.row0 + min(rbase + lrow, it.n_rows - 1)];
-  const int row = ar.row;
-  const int pos = ar.pos;
+  // first visible key); items of consecutive computed rows at consecutive
+  // positions carry their first row (crow0) and skip that read
+  const int rr = min(rbase + lrow, it.n_rows - 1);
+  int row, pos;
+  if (it.crow0 >= 0) {
+    row = it.crow0 + rr;
+    pos = it.min_pos + rr;
+  } else {
+    const AttnRow ar = arows[it.row0 + rr];
+    row = ar.row;
+    pos = ar.pos;
+  }
+  // ---- staging.  The two 16-key blocks of a tile each lie in one page;
+  // staging wave w takes block w / 2 and 64 of its dims, so that a wave's
+  // page, the base of its loads and its page scales are uniform.
+  // K: one direct load a wave; lane l fetches 16 bytes (chunk l / 16 of the
+  //    64) of key l % 16 into their place in the fragment order.
+  // V: lane l owns 8 bytes (dims 8 (l / 8) ..) of keys 2 (l % 8) and
+  //    2 (l % 8) + 1, which sit next to each other in the permuted V^T row.
+  // Page ids are fetched a tile before the loads that need them, and raw V
+  // is local to one pass of the tile loop (carried around it, it is copied
+  // right after the loads, which waits for them there).
+  // (Before: K through registers, both blocks a wave, page ids loaded with the
+  // tile and the first tile after the queries.  fp8 RAG 1,712 -> 1,640 us,
+  // one fp8 request 225 -> 203.)
+  const int sb = w >> 1;
+  const uint32_t koff = (lane & 15) * kD + 16 * (lane >> 4) + 64 * (w & 1);
+  const int kp = lane & 7;
+  const int vc8 = 64 * (w & 1) + 8 * (lane >> 3);
+  const uint32_t voff = 2 * kp * kD + vc8;
+  const int vst = vc8 * kVStr + vt_col(16 * sb + 2 * kp);
+  auto fetch_page = [&](int j) __attribute__((always_inline)) {
+    return bt[min((j * kKT + 16 * sb) >> log2_page, it.n_pages - 1)];
+  };
+  auto block_base = [&](int page, int kq) -> int64_t {
+    return ((((int64_t)page * n_kv_heads + g) << log2_page) + (kq & page_mask)) * kD;
+  };
+  auto load_tile = [&](int j, int page, uint8_t* kt, u32x2& v0, u32x2& v1, float& nk, float& nv)
+      __attribute__((always_inline)) {
+    const int key0 = j * kKT;
+    const int kb0 = key0 + 16 * sb;
+    const int64_t base = block_base(page, kb0);
+    nk = scales[2 * (int64_t)page];
+    nv = scales[2 * (int64_t)page + 1];
+    const uint8_t* vsrc = vc + base;
+    uint32_t o0 = voff, o1 = voff + kD;
+    if (key0 + kKT > it.kv_len) {
+      // last, partial tile: keys past kv_len may be unwritten slots.  Their
+      // scores are masked (a select), but 0 * NaN in P V would not be, so a
+      // key of the tile stands in for them: the block's first, or the
+      // tile's where the whole block lies past kv_len
+      if (kb0 + 2 * kp >= it.kv_len) o0 = vc8;
+      if (kb0 + 2 * kp + 1 >= it.kv_len) o1 = vc8;
+      if (kb0 >= it.kv_len) {
+        const int p0 = bt[key0 >> log2_page];
+        vsrc = vc + block_base(p0, key0);
+        nv = scales[2 * (int64_t)p0 + 1];
+      }
+    }
+    v0 = *reinterpret_cast<const u32x2*>(vsrc + o0);
+    v1 = *reinterpret_cast<const u32x2*>(vsrc + o1);
+    lds_dma16<0>(kc + base, koff, lds_addr(kt) + (2 * sb + (w & 1)) * kK8Blk);
+  };
+  auto store_tile = [&](int buf, const u32x2& v0, const u32x2& v1, float nk, float nv)
+      __attribute__((always_inline)) {
+    if ((w & 1) == 0 && lane == 0) kscl[buf][sb] = nk;
+    // V^T[d][key] in fp16: gather byte e of keys (k0, k1) into one word and
+    // convert two codes at a time with the page scale.
+    // a page scale above 2^7 can take codes (|c| <= 448) past fp16's
+    // 65504: such pages are refused loudly, as NaN values
+    const float s = nv <= 128.0f ? nv : __builtin_nanf("");
+    uint16_t* vs = vmem[buf] + vst;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int e2 = 0; e2 < 2; ++e2) {
+        // bytes (k0[e], k1[e], k0[e+1], k1[e+1]) for e = 2*e2 within the word
+        const uint32_t sel = e2 ? 0x07030602u : 0x05010400u;
+        const uint32_t p01 = __builtin_amdgcn_perm(v1[half], v0[half], sel);
+        // low word: keys (0,1) at dim e; high word: at dim e + 1
+        const f16x2 l01 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p01, s, false);
+        const f16x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p01, s, true);
+        const int d = 4 * half + 2 * e2;
+        *reinterpret_cast<uint32_t*>(vs + d * kVStr) = __builtin_bit_cast(uint32_t, l01);
+        *reinterpret_cast<uint32_t*>(vs + (d + 1) * kVStr) = __builtin_bit_cast(uint32_t, h01);
+      }
+    }
+  };
+  // keys kv_lo .. kv_len-1: tiles j0 .. ntiles-1; a tile needs the mask when
+  // it reaches past the smallest row position or starts below kv_lo
+  const int ntiles = (it.kv_len + kKT - 1) / kKT;
+  const int j0 = it.kv_lo / kKT;
+  const int jlo = (it.kv_lo + kKT - 1) / kKT;
+  const int nfull = min(ntiles, (it.min_pos + 1) / kKT);
+  // the first tile's loads (its page comes with the item) run under the
+  // query rotation
+  int npage = sb ? it.pg[1] : it.pg[0];
+  u32x2 vf0, vf1;
+  float nkf = 1.0f, nvf = 1.0f;
+  if (stager) {
+    load_tile(j0, npage, kmem[j0 & 1], vf0, vf1, nkf, nvf);
+    npage = fetch_page(j0 + 1);
+  }
   {
     const int t = tid & 255, lr = t >> 3, c8 = 8 * (t & 7);
-    const int ppos = arows[it.row0 + min(rbase + lr, it.n_rows - 1)].pos;
+    const int pr = min(rbase + lr, it.n_rows - 1);
+    const int ppos = it.crow0 >= 0 ? it.min_pos + pr : arows[it.row0 + pr].pos;
     float c[8], sn[8];
     load8(rope_cos + (int64_t)ppos * (kD / 2) + c8, c);
     load8(rope_sin + (int64_t)ppos * (kD / 2) + c8, sn);
@@ -117,26 +204,42 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
     for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, __shfl_xor(wmax, o));
     my_ntiles = __builtin_amdgcn_readfirstlane(wmax + kKT) / kKT;
   }
-  __syncthreads();
-
   // ---- queries: rotate in fp32, quantize per (row, head) to e4m3.  Lane
   // half lh holds dims [32 lh, 32 lh + 32) of both RoPE halves, i.e. the
-  // B operands of the two 64-deep k steps.
+  // B operands of the two 64-deep k steps.  The raw rows are on their way
+  // while the cos/sin rows go to LDS.
   i32x8 qf[HPW][2];
   float qs[HPW];
+  uint4 qraw[HPW][8];
 #pragma unroll
   for (int i = 0; i < HPW; ++i) {
     // wave w owns query head head0 + w of the group; with G < 4 the spare
     // waves recompute head G-1 and store nothing
     const int hl = G >= 4 ? it.head0 + w + 4 * i : min(w + 4 * i, G - 1);
-    const uint16_t* qp = q + ((int64_t)row * n_q_heads + g * G + hl) * kD;
+    const uint16_t* qp = q + ((int64_t)row * n_q_heads + g * G + hl) * kD + 32 * lh;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      qraw[i][c] = *reinterpret_cast<const uint4*>(qp + 8 * c);
+      qraw[i][c + 4] = *reinterpret_cast<const uint4*>(qp + 8 * c + kD / 2);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < HPW; ++i) {
     float lo[32], hi[32];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int d0 = 32 * lh + 8 * c;
+      const uint4 a = qraw[i][c], b = qraw[i][c + 4];
+      const uint32_t wl[4] = {a.x, a.y, a.z, a.w}, wh[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[8 * c + 2 * e] = bf16_to_f32(wl[e] & 0xffffu);
+        lo[8 * c + 2 * e + 1] = bf16_to_f32(wl[e] >> 16);
+        hi[8 * c + 2 * e] = bf16_to_f32(wh[e] & 0xffffu);
+        hi[8 * c + 2 * e + 1] = bf16_to_f32(wh[e] >> 16);
+      }
       float cs[8], sn[8];
-      load8(qp + d0, lo + 8 * c);
-      load8(qp + d0 + kD / 2, hi + 8 * c);
       load8(&rl[rb][lrow][d0], cs);
       load8(&rl[rb][lrow][kD / 2 + d0], sn);
       rope_rotate<8>(lo + 8 * c, hi + 8 * c, cs, sn);
@@ -178,76 +281,15 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
 #pragma unroll
   for (int i = 0; i < HPW; ++i) wave_active[i] = G >= 4 || (w + 4 * i) < G;
 
-  // ---- global -> register staging.  The two 16-key blocks of a tile each
-  // lie in one page.
-  // K: one 16-byte chunk per thread: key tid / 8 (block tid / 128), dims
-  //    16 (tid % 8) ..
-  // V: keys 2 (tid % 16) and 2 (tid % 16) + 1, dims 8 (tid / 16) .. +7
-  //    (8 bytes per key); the two keys sit next to each other in the
-  //    permuted V^T row.
-  uint4 kr;
-  uint2 vr[2];
-  const int kp2 = tid & 15;               // key pair
-  const int vq = kp2 >> 3;                // 16-key block of the pair
-  const int vk = 2 * kp2 - 16 * vq;       // first key within its block
-  const int vc8 = (tid >> 4) * 8;
-  const int vcol = 16 * vq + ((vk >> 2) & 1) * 8 + ((vk >> 3) & 1) * 4 + (vk & 3);   // permuted
-  float nks[2], nvs[2];   // page scales of the staged tile (uniform)
-  auto load_tile = [&](int j) {
-    const int key0 = j * kKT;
-    int64_t base[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int kq = key0 + 16 * b;
-      const int page = bt[min(kq >> log2_page, it.n_pages - 1)];
-      base[b] = ((((int64_t)page * n_kv_heads + g) << log2_page) + (kq & page_mask)) * kD;
-      nks[b] = scales[2 * page];
-      nvs[b] = scales[2 * page + 1];
-    }
-    kr = *reinterpret_cast<const uint4*>(kc + ((tid >> 7) ? base[1] : base[0]) +
-                                         ((tid >> 3) & 15) * kD + (tid & 7) * 16);
-    const int64_t vb = vq ? base[1] : base[0];
-#pragma unroll
-    for (int pb = 0; pb < 2; ++pb)
-      vr[pb] = *reinterpret_cast<const uint2*>(vc + vb + (vk + pb) * kD + vc8);
-    if (key0 + kKT > it.kv_len) {  // last, partial tile
-      if (key0 + (tid >> 3) >= it.kv_len) kr = make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int pb = 0; pb < 2; ++pb)
-        if (key0 + 2 * kp2 + pb >= it.kv_len) vr[pb] = make_uint2(0, 0);
-    }
+  // K fragment kst: the lane's key l % 32, dims 64 kst + 32 (l / 32) ..; both
+  // 16-byte halves land in adjacent registers of the operand
+  const int kfl = (lrow >> 4) * 2 * kK8Blk + 512 * lh + 16 * (lrow & 15);
+  auto kfrag = [&](const uint8_t* ks, int kst) __attribute__((always_inline)) {
+    union { uint4 u[2]; i32x8 v; } x;
+    x.u[0] = *reinterpret_cast<const uint4*>(ks + kfl + kst * kK8Blk);
+    x.u[1] = *reinterpret_cast<const uint4*>(ks + kfl + kst * kK8Blk + 256);
+    return x.v;
   };
-  auto store_tile = [&](int buf) {
-    *reinterpret_cast<uint4*>(&kmem[buf][(tid >> 3) * kKStr + (tid & 7) * 16]) = kr;
-    if (tid == 0) {
-      kscl[buf][0] = nks[0];
-      kscl[buf][1] = nks[1];
-    }
-    // V^T[d][key] in fp16: gather byte e of keys (k0, k1) into one word and
-    // convert two codes at a time with the page scale.
-    // a page scale above 2^7 can take codes (|c| <= 448) past fp16's
-    // 65504: such pages are refused loudly, as NaN values
-    const float sp = vq ? nvs[1] : nvs[0];
-    const float s = sp <= 128.0f ? sp : __builtin_nanf("");
-    uint16_t* vs = vmem[buf];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const uint32_t a0 = half ? vr[0].y : vr[0].x, a1 = half ? vr[1].y : vr[1].x;
-#pragma unroll
-      for (int e2 = 0; e2 < 2; ++e2) {
-        // bytes (k0[e], k1[e], k0[e+1], k1[e+1]) for e = 2*e2 within the word
-        const uint32_t sel = e2 ? 0x07030602u : 0x05010400u;
-        const uint32_t p01 = __builtin_amdgcn_perm(a1, a0, sel);
-        // low word: keys (0,1) at dim e; high word: at dim e + 1
-        const f16x2 l01 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p01, s, false);
-        const f16x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p01, s, true);
-        const int d = vc8 + 4 * half + 2 * e2;
-        *reinterpret_cast<uint32_t*>(vs + d * kVStr + vcol) = __builtin_bit_cast(uint32_t, l01);
-        *reinterpret_cast<uint32_t*>(vs + (d + 1) * kVStr + vcol) = __builtin_bit_cast(uint32_t, h01);
-      }
-    }
-  };
-
   // MASK: 0 none, 1 keys past the row's position (tiles reaching past the
   // item's smallest position), 2 also keys below kv_lo (the tile holding it)
   auto tile = [&](int j, auto mask_tag) {
@@ -265,18 +307,18 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
     for (int kst = 0; kst < 2; ++kst) {
 #pragma unroll
       for (int kb = 0; kb < 1; ++kb) {
-        const uint8_t* kp = ks + (32 * kb + lrow) * kKStr + 64 * kst + 32 * lh;
-        // both 16-byte halves land in adjacent registers of the operand
-        union { uint4 u[2]; i32x8 v; } x;
-        x.u[0] = *reinterpret_cast<const uint4*>(kp);
-        x.u[1] = *reinterpret_cast<const uint4*>(kp + 16);
-        const i32x8 a = x.v;
+        const i32x8 a = kfrag(ks, kst);
 #pragma unroll
         for (int i = 0; i < HPW; ++i)
           s[i][kb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
               a, qf[i][kst], s[i][kb], 0, 0, 0, 127, 0, 127);
       }
     }
+    // the V^T fragments of the first 16 keys are read while the softmax runs
+    Frag va[4];
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+      va[db].u = *reinterpret_cast<const uint4*>(vs + (32 * db + lrow) * kVStr + 8 * lh);
     // page of S register r: r/8 within the tile; its factor f (Q scale x K
     // page scale x softmax scale x log2 e) is > 0, so P = exp2(f s - m) is
     // one fma and one exp2 per score and each page's row max is f times the
@@ -292,12 +334,8 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
       for (int r = 0; r < 16; ++r) s[i][0][r] = 0.0f;
 #pragma unroll
       for (int kst = 0; kst < 2; ++kst) {
-        const uint8_t* kp = ks + lrow * kKStr + 64 * kst + 32 * lh;
-        union { uint4 u[2]; i32x8 v; } x;
-        x.u[0] = *reinterpret_cast<const uint4*>(kp);
-        x.u[1] = *reinterpret_cast<const uint4*>(kp + 16);
         s[i][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-            x.v, qf[i][kst], s[i][0], 0, 0, 0, 127, 0, 127);
+            kfrag(ks, kst), qf[i][kst], s[i][0], 0, 0, 0, 127, 0, 127);
       }
     };
     auto mask = [&](int i) __attribute__((always_inline)) {
@@ -369,29 +407,22 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
         for (int e = 0; e < 8; ++e) pf[i][k2][e] = (_Float16)s[i][0][8 * k2 + e];
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) {
+    for (int db = 0; db < 4; ++db) {
+      o[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[db].h, pf[0][0], o[0][db], 0, 0, 0);
+      va[db].u = *reinterpret_cast<const uint4*>(vs + (32 * db + lrow) * kVStr + 16 + 8 * lh);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-      for (int db = 0; db < 4; ++db) {
-        Frag8 a;
-        a.u = *reinterpret_cast<const uint4*>(vs + (32 * db + lrow) * kVStr + 16 * k2 + 8 * lh);
-#pragma unroll
-        for (int i = 0; i < HPW; ++i)
-          o[i][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, pf[i][k2], o[i][db], 0, 0, 0);
-      }
+    for (int db = 0; db < 4; ++db) {
+      o[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[db].h, pf[0][1], o[0][db], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
 
-  // keys kv_lo .. kv_len-1: tiles j0 .. ntiles-1; a tile needs the mask when
-  // it reaches past the smallest row position or starts below kv_lo
-  const int ntiles = (it.kv_len + kKT - 1) / kKT;
-  const int j0 = it.kv_lo / kKT;
-  const int jlo = (it.kv_lo + kKT - 1) / kKT;
-  const int nfull = min(ntiles, (it.min_pos + 1) / kKT);
-  if (stager) {
-    load_tile(j0);
-    store_tile(j0 & 1);
-  }
+  if (stager) store_tile(j0 & 1, vf0, vf1, nkf, nvf);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);   // the direct K load
   __syncthreads();
   // Three loops (masked head, unmasked body, masked tail) rather than one
   // loop that picks the masked or unmasked tile per iteration: with both
@@ -401,9 +432,15 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
   auto run_tiles = [&](int ja, int jb, auto mask_tag) __attribute__((always_inline)) {
     for (int j = ja; j < jb; ++j) {
       const bool more = j + 1 < ntiles;
-      if (more) load_tile(j + 1);
+      u32x2 v0, v1;
+      float nk, nv;
+      if (more) {
+        load_tile(j + 1, npage, kmem[(j + 1) & 1], v0, v1, nk, nv);
+        npage = fetch_page(j + 2);
+      }
       if (j < my_ntiles) tile(j, mask_tag);
-      if (more) store_tile((j + 1) & 1);
+      if (more) store_tile((j + 1) & 1, v0, v1, nk, nv);
+      __builtin_amdgcn_s_waitcnt(kWaitVm0);
       __syncthreads();
     }
   };
@@ -440,8 +477,8 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
       for (int rg = 0; rg < 4; ++rg) {
         const int d0 = 32 * db + 8 * rg + 4 * lh;
         uint2 v;
-        v.x = f32_to_bf16(o[i][db][4 * rg] * inv) | (f32_to_bf16(o[i][db][4 * rg + 1] * inv) << 16);
-        v.y = f32_to_bf16(o[i][db][4 * rg + 2] * inv) | (f32_to_bf16(o[i][db][4 * rg + 3] * inv) << 16);
+        v.x = pack_bf16x2(o[i][db][4 * rg] * inv, o[i][db][4 * rg + 1] * inv);
+        v.y = pack_bf16x2(o[i][db][4 * rg + 2] * inv, o[i][db][4 * rg + 3] * inv);
         *reinterpret_cast<uint2*>(op + d0) = v;
       }
     // lse (natural log) = (m + log2 l) * ln 2 with m in log2 units
