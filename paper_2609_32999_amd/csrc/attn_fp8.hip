@@ -48,8 +48,13 @@ __device__ __forceinline__ int page_scale_exp(float amax) {
 // row block b; the first four waves stage every K/V tile for all of them
 // (three row blocks share each staged tile, which cuts the KV reads per row
 // threefold).
-template <int G, int R>
-__global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
+// KS: wave groups per row block (R = 1).  The item's key tiles are dealt to
+// KS groups of four waves, each staging its own tiles and keeping its own
+// running softmax; group 0 merges them through LDS at the end.  Used where a
+// launch has too few items to fill the chip: it then lasts as long as its
+// longest item, and the groups cut that into KS parts.
+template <int G, int R, int KS>
+__global__ __launch_bounds__(256 * R * KS, 3) void attn_fp8_kernel(
     const uint16_t* __restrict__ q, const uint8_t* __restrict__ kc,
     const uint8_t* __restrict__ vc, const float* __restrict__ scales,
     const AttnItem* __restrict__ items, const int32_t* __restrict__ bts,
@@ -58,10 +63,11 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
     float* __restrict__ lse, int n_q_heads, int n_kv_heads, int log2_page,
     float scale_log2e) {
   constexpr int HPW = 1;  // query heads per wave
-  __shared__ __attribute__((aligned(16))) uint8_t kmem[2][kK8Bytes];
-  __shared__ __attribute__((aligned(16))) uint16_t vmem[2][kVElems];
+  static_assert(KS == 1 || (KS == 3 && R == 1), "wave groups");
+  __shared__ __attribute__((aligned(16))) uint8_t klds[KS][2][kK8Bytes];
+  __shared__ __attribute__((aligned(16))) uint16_t vlds[KS][2][kVElems];
   // K page scales of each staged tile's two 16-key blocks
-  __shared__ float kscl[2][2];
+  __shared__ float slds[KS][2][2];
   // cos (dims 0 .. d/2-1) and sin (d/2 ..) at each row's position, per row
   // block, loaded once and shared by its four head waves (rows padded by 4
   // floats so that the 32 rows of a fragment read fall in different banks)
@@ -72,8 +78,12 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
   const int tid = threadIdx.x;
   const int wg = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = wg & 3;                  // query head slot
-  const int rb = wg >> 2;                // row block
-  const bool stager = wg < 4;            // waves that stage K and V
+  const int rb = KS == 1 ? wg >> 2 : 0;  // row block
+  const int kg = KS == 1 ? 0 : wg >> 2;  // wave group
+  const bool stager = KS > 1 || wg < 4;  // waves that stage K and V
+  auto kmem = klds[kg];
+  auto vmem = vlds[kg];
+  auto kscl = slds[kg];
   const int lane = tid & 63;
   const int lrow = lane & 31;
   const int lh = lane >> 5;
@@ -180,13 +190,16 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
   // the first tile's loads (its page comes with the item) run under the
   // query rotation
   int npage = sb ? it.pg[1] : it.pg[0];
+  int j = j0 + kg;   // this wave group's tile
+  if (KS > 1 && kg > 0) npage = fetch_page(j);
   u32x2 vf0, vf1;
   float nkf = 1.0f, nvf = 1.0f;
-  if (stager) {
-    load_tile(j0, npage, kmem[j0 & 1], vf0, vf1, nkf, nvf);
-    npage = fetch_page(j0 + 1);
+  const bool first = stager && (KS == 1 || j < ntiles);
+  if (first) {
+    load_tile(j, npage, kmem[j & 1], vf0, vf1, nkf, nvf);
+    npage = fetch_page(j + KS);
   }
-  {
+  if (KS == 1 || kg == 0) {
     const int t = tid & 255, lr = t >> 3, c8 = 8 * (t & 7);
     const int pr = min(rbase + lr, it.n_rows - 1);
     const int ppos = it.crow0 >= 0 ? it.min_pos + pr : arows[it.row0 + pr].pos;
@@ -370,7 +383,10 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
         ls[r & 3] += p;
       }
       const float lt = (ls[0] + ls[1]) + (ls[2] + ls[3]);
-      if (__builtin_amdgcn_ballot_w64(!(lt <= kLazySum) || m[i] == -INFINITY)) {
+      // a row that sees no key of its wave group's tiles up to here waits
+      // with m at -inf
+      const bool sees = KS == 1 || MASK != 1 || pos - 4 * lh >= j * kKT;
+      if (__builtin_amdgcn_ballot_w64(!(lt <= kLazySum) || (m[i] == -INFINITY && sees))) {
         scores(i);
         mask(i);
         float mb[2];
@@ -421,7 +437,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
     }
   };
 
-  if (stager) store_tile(j0 & 1, vf0, vf1, nkf, nvf);
+  if (first) store_tile(j & 1, vf0, vf1, nkf, nvf);
   __builtin_amdgcn_s_waitcnt(kWaitVm0);   // the direct K load
   __syncthreads();
   // Three loops (masked head, unmasked body, masked tail) rather than one
@@ -429,14 +445,15 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
   // variants in one loop body the compiler kept about 90 more registers
   // live.  Tiles past a row block's last row are fully masked for it and
   // skipped (only in the masked tail).
-  auto run_tiles = [&](int ja, int jb, auto mask_tag) __attribute__((always_inline)) {
-    for (int j = ja; j < jb; ++j) {
-      const bool more = j + 1 < ntiles;
+  // (A group's tiles alternate between its two buffers: KS is odd.)
+  auto run_tiles = [&](int jb, auto mask_tag) __attribute__((always_inline)) {
+    for (; j < jb; j += KS) {
+      const bool more = j + KS < ntiles;
       u32x2 v0, v1;
       float nk, nv;
       if (more) {
-        load_tile(j + 1, npage, kmem[(j + 1) & 1], v0, v1, nk, nv);
-        npage = fetch_page(j + 2);
+        load_tile(j + KS, npage, kmem[(j + 1) & 1], v0, v1, nk, nv);
+        npage = fetch_page(j + 2 * KS);
       }
       if (j < my_ntiles) tile(j, mask_tag);
       if (more) store_tile((j + 1) & 1, v0, v1, nk, nv);
@@ -445,28 +462,77 @@ __global__ __launch_bounds__(256 * R, 3) void attn_fp8_kernel(
     }
   };
   // the waves of the other row blocks stage nothing
-  auto run_tiles_ns = [&](int ja, int jb, auto mask_tag) __attribute__((always_inline)) {
-    for (int j = ja; j < jb; ++j) {
+  auto run_tiles_ns = [&](int jb, auto mask_tag) __attribute__((always_inline)) {
+    for (; j < jb; ++j) {
       if (j < my_ntiles) tile(j, mask_tag);
       __syncthreads();
     }
   };
-  const int jl = min(ntiles, max(j0, jlo));
   if (stager) {
-    run_tiles(j0, jl, std::integral_constant<int, 2>{});
-    run_tiles(jl, max(jl, nfull), std::integral_constant<int, 0>{});
-    run_tiles(max(jl, nfull), ntiles, std::integral_constant<int, 1>{});
+    run_tiles(min(ntiles, jlo), std::integral_constant<int, 2>{});
+    run_tiles(nfull, std::integral_constant<int, 0>{});
+    run_tiles(ntiles, std::integral_constant<int, 1>{});
   } else {
-    run_tiles_ns(j0, jl, std::integral_constant<int, 2>{});
-    run_tiles_ns(jl, max(jl, nfull), std::integral_constant<int, 0>{});
-    run_tiles_ns(max(jl, nfull), ntiles, std::integral_constant<int, 1>{});
+    run_tiles_ns(min(ntiles, jlo), std::integral_constant<int, 2>{});
+    run_tiles_ns(nfull, std::integral_constant<int, 0>{});
+    run_tiles_ns(ntiles, std::integral_constant<int, 1>{});
+  }
+
+  if constexpr (KS > 1) {
+    // every group passes one barrier per tile of group 0
+    if (j < j0 + kg + (ntiles - j0 + KS - 1) / KS * KS) __syncthreads();
+    // weights 2^(m_g - M), M the row's maximum over the groups (0 for a group
+    // that saw none of the row's keys); the outputs go through the V buffers,
+    // 32 head dims at a time
+    auto ml = reinterpret_cast<float (*)[4][32][2]>(&rl[0][0][0]);
+    const float lw = l[0] + __shfl_xor(l[0], 32);
+    if (lh == 0) {
+      ml[kg][w][lrow][0] = m[0];
+      ml[kg][w][lrow][1] = lw;
+    }
+    __syncthreads();
+    float mx = -INFINITY, lt = 0.0f;
+#pragma unroll
+    for (int i = 0; i < KS; ++i) mx = fmaxf(mx, ml[i][w][lrow][0]);
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const float mi = ml[i][w][lrow][0];
+      lt += mi == -INFINITY ? 0.0f : ml[i][w][lrow][1] * __builtin_amdgcn_exp2f(mi - mx);
+    }
+    const float f = m[0] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m[0] - mx);
+    m[0] = mx;
+    l[0] = lt;
+    float4* xb = reinterpret_cast<float4*>(&vlds[0][0][0]);   // [group - 1][wave][4][64]
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      if (db) __syncthreads();
+      if (kg > 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          xb[(((kg - 1) * 4 + w) * 4 + i) * 64 + lane] =
+              make_float4(o[0][db][4 * i] * f, o[0][db][4 * i + 1] * f,
+                          o[0][db][4 * i + 2] * f, o[0][db][4 * i + 3] * f);
+      }
+      __syncthreads();
+      if (kg == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 a = xb[(w * 4 + i) * 64 + lane], b = xb[((4 + w) * 4 + i) * 64 + lane];
+          o[0][db][4 * i] = fmaf(o[0][db][4 * i], f, a.x) + b.x;
+          o[0][db][4 * i + 1] = fmaf(o[0][db][4 * i + 1], f, a.y) + b.y;
+          o[0][db][4 * i + 2] = fmaf(o[0][db][4 * i + 2], f, a.z) + b.z;
+          o[0][db][4 * i + 3] = fmaf(o[0][db][4 * i + 3], f, a.w) + b.w;
+        }
+      }
+    }
+    if (kg > 0) return;
   }
 
   // ---- epilogue
 #pragma unroll
   for (int i = 0; i < HPW; ++i) {
     if (!wave_active[i]) continue;
-    const float lt = l[i] + __shfl_xor(l[i], 32);
+    const float lt = KS > 1 ? l[i] : l[i] + __shfl_xor(l[i], 32);
     if (rbase + lrow >= it.n_rows) continue;
     const float inv = 1.0f / lt;
     const int hq = g * G + (G >= 4 ? it.head0 : 0) + w + 4 * i;
@@ -506,12 +572,15 @@ hipError_t launch_attn_e4m3(const tsr_plan* p, const AttnItem* items, int32_t n_
   const float sl2e = (float)((double)p->scale * 1.4426950408889634);
 #define TSR_FP8(GG)                                                                   \
   if (p->row_blocks == kMaxRowBlocks)                                                 \
-    TSR_FP8_R(GG, kMaxRowBlocks);                                                     \
+    TSR_FP8_R(GG, kMaxRowBlocks, 1);                                                  \
+  else if (p->wave_groups == kWaveGroups)                                             \
+    TSR_FP8_R(GG, 1, kWaveGroups);                                                    \
   else                                                                                \
-    TSR_FP8_R(GG, 1)
-#define TSR_FP8_R(GG, RB)                                                             \
-  hipLaunchKernelGGL((attn_fp8_kernel<GG, RB>), dim3(n_items), dim3(256 * (RB)), 0, s, \
-                     static_cast<const uint16_t*>(q), static_cast<const uint8_t*>(req_k), \
+    TSR_FP8_R(GG, 1, 1)
+#define TSR_FP8_R(GG, RB, KS)                                                         \
+  hipLaunchKernelGGL((attn_fp8_kernel<GG, RB, KS>), dim3(n_items), dim3(256 * (RB) * (KS)), \
+                     0, s, static_cast<const uint16_t*>(q),                           \
+                     static_cast<const uint8_t*>(req_k),                              \
                      static_cast<const uint8_t*>(req_v), req_scale, items,            \
                      p->dev.block_tables, p->dev.attn_rows, p->dev.rope_cos,          \
                      p->dev.rope_sin, static_cast<uint16_t*>(out), lse, m.n_q_heads,  \

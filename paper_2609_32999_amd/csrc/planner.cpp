@@ -481,6 +481,14 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   } else {
     build_items(1);
   }
+  // An e4m3 launch of fewer one-row-block items than the chip holds at once
+  // lasts as long as its longest item, whose key tiles go to kWaveGroups wave
+  // groups then, if it has enough of them.
+  const bool few = (int64_t)items.size() < kFullLaunchItems;
+  p->wave_groups = mfma && !bf16_kv && p->row_blocks == 1 && few &&
+                           max_blocks >= 2 * kMinGroupTiles
+                       ? kWaveGroups
+                       : 1;
   p->rows_grouped = !std::is_sorted(ord.begin(), ord.end());
   std::vector<AttnRow> attn_rows((size_t)T);
   for (int32_t i = 0; i < T; ++i) attn_rows[i] = AttnRow{ord[i], p->row_pos[ord[i]]};

@@ -27,6 +27,14 @@ constexpr int kTileRows = 32;
 // grouping) the two were level.
 constexpr int kMaxRowBlocks = 3;
 constexpr double kMinGroupedRowBlockUse = 0.6;
+// Wave groups that share the key tiles of a one-row-block e4m3 item, in
+// launches of fewer than kFullLaunchItems items whose longest spans at least
+// kMinGroupTiles key tiles.  One fp8 RAG request (464 items, up to 260 tiles)
+// 202 -> 133 us, with every chunk cached (88 items) 186 -> 119, four chunks
+// (168 items, 67 tiles) 56 -> 42, 648 items 213 -> 199; four requests of 17
+// tiles 20 -> 26.
+constexpr int kWaveGroups = 3;
+constexpr int kMinGroupTiles = 32;
 // Compute units of the GPU (MI355X).
 constexpr int kNumCus = 256;
 // Attention launches with at least this many (request, KV head) groups per
@@ -198,6 +206,7 @@ struct tsr_plan {
   int32_t n_items_part[2];
   int32_t max_kv_len;
   int32_t row_blocks;       // row blocks per attention item (1, kPipeRowBlocks or kMaxRowBlocks)
+  int32_t wave_groups;      // wave groups per row block (kWaveGroups: e4m3, few items)
   // key-range split items: merge descriptors (part 0's first) and buffer
   int32_t n_combine;
   int32_t n_combine_part[2];
