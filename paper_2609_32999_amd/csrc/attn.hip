@@ -314,6 +314,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
   constexpr bool kQinLds = AK;
   constexpr int kQBytes = kQinLds ? 4 * R * 8 * 1024 : 0;
   __shared__ __attribute__((aligned(16))) uint8_t pro[kRlBytes > kQBytes ? kRlBytes : kQBytes];
+  static_assert(4 * R * kOutLds <= (int)sizeof(pro), "outputs go through it");
   auto rl = reinterpret_cast<float (*)[kTileRows][kD + 4]>(pro);
 
   const AttnItem it = items[blockIdx.x];
@@ -749,41 +750,36 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
 
   // ---- epilogue: normalise, round to bf16, store rows of this tile
   const float lt = l + __shfl_xor(l, 32);
-  if (!wave_active || rbase + lrow >= it.n_rows) return;
+  const int n_mine = min(kTileRows, it.n_rows - rbase);   // this row block's rows
+  if (!wave_active || n_mine <= 0) return;
   float inv = 1.0f / lt;
-  {
-    if (it.part_slot >= 0) {
-      // one key range of a split item: normalized rows and log-sum-exp in
-      // fp32 to this row block's slot, merged by attn_merge_kernel; a row
-      // that sees no key of the range weighs nothing there (0, -inf)
-      if (m == -INFINITY) inv = 0.0f;
-      const int64_t slot = it.part_slot + (int64_t)rb * it.n_parts;
-      const int64_t sr = (slot * kTileRows + lrow) * kSplitHeads + w;
-      float* po = split_o + sr * kD;
+  if (it.part_slot >= 0) {
+    // one key range of a split item: normalized rows and log-sum-exp in
+    // fp32 to this row block's slot, merged by attn_merge_kernel; a row
+    // that sees no key of the range weighs nothing there (0, -inf)
+    if (lrow >= n_mine) return;
+    if (m == -INFINITY) inv = 0.0f;
+    const int64_t slot = it.part_slot + (int64_t)rb * it.n_parts;
+    const int64_t sr = (slot * kTileRows + lrow) * kSplitHeads + w;
+    float* po = split_o + sr * kD;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg)
-          *reinterpret_cast<float4*>(po + 32 * db + 8 * rg + 4 * lh) =
-              make_float4(o[db][4 * rg] * inv, o[db][4 * rg + 1] * inv,
-                          o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-      if (lh == 0) split_lse[sr] = m == -INFINITY ? -INFINITY : m * scale + logf(lt);
-      return;
-    }
+      for (int rg = 0; rg < 4; ++rg)
+        *reinterpret_cast<float4*>(po + 32 * db + 8 * rg + 4 * lh) =
+            make_float4(o[db][4 * rg] * inv, o[db][4 * rg + 1] * inv,
+                        o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
+    if (lh == 0) split_lse[sr] = m == -INFINITY ? -INFINITY : m * scale + logf(lt);
+    return;
   }
   const int hq = g * G + (G >= 4 ? it.head0 : 0) + w;
-  uint16_t* op = out + ((int64_t)row * n_q_heads + hq) * kD;
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      const int d0 = 32 * db + 8 * rg + 4 * lh;
-      uint2 v;
-      v.x = pack_bf16x2(o[db][4 * rg] * inv, o[db][4 * rg + 1] * inv);
-      v.y = pack_bf16x2(o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-      *reinterpret_cast<uint2*>(op + d0) = v;
-    }
-  if (lse && lh == 0) lse[(int64_t)row * n_q_heads + hq] = m * scale + logf(lt);
+  if (lse && lh == 0 && lrow < n_mine)
+    lse[(int64_t)row * n_q_heads + hq] = m * scale + logf(lt);
+  // (the cos/sin rows' LDS is free: every wave is past the last tile's barrier)
+  store_out(o, inv, pro + (tid >> 6) * kOutLds, lane, n_mine, out, [&](int r) -> int64_t {
+    const int cr = it.crow0 >= 0 ? it.crow0 + rbase + r : arows[it.row0 + rbase + r].row;
+    return ((int64_t)cr * n_q_heads + hq) * kD;
+  });
 }
 
 int ilog2(int x) {

@@ -75,6 +75,47 @@ __device__ __forceinline__ void lds_dma16(const void* base, uint32_t off, uint32
 }
 #pragma clang diagnostic pop
 
+// One wave's normalized output rows (the O^T accumulators: lane l holds row
+// l % 32, dims 32 db + 8 rg + 4 (l / 32) .. + 3 in o[db][4 rg ..]) as bf16 to
+// out rows of kD elements, through kOutLds bytes of LDS that are the wave's
+// own.  Stored from the accumulators, an instruction touches 32 rows 16 bytes
+// at a time; from LDS it writes 64 bytes of each of 16 rows, half the lines
+// for the same bytes.  RAG-8B LOCAL attention 251 -> 243 us, GLOBAL 563 -> 557,
+// agent memory 1,630 -> 1,614, fp8 RAG 1,649 -> 1,620; outputs keep their bits.
+// row_off(r): element offset of row r in out; rows r < n are stored.
+constexpr int kOutStr = 80;                      // bytes per row of a 32-dim block
+constexpr int kOutLds = 32 * kOutStr;
+template <typename RowOff>
+__device__ __forceinline__ void store_out(const f32x16 (&o)[4], float inv, uint8_t* lds,
+                                          int lane, int n, uint16_t* __restrict__ out,
+                                          RowOff row_off) {
+  typedef uint32_t lds2 __attribute__((ext_vector_type(2), may_alias));
+  typedef uint32_t lds4 __attribute__((ext_vector_type(4), may_alias));
+  const int lrow = lane & 31, lh = lane >> 5, r4 = lane >> 2, c4 = lane & 3;
+  const int64_t off[2] = {row_off(min(r4, n - 1)), row_off(min(r4 + 16, n - 1))};
+#pragma unroll
+  for (int db = 0; db < 4; ++db) {
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      const bf16x4 v = {(__bf16)(o[db][4 * rg] * inv), (__bf16)(o[db][4 * rg + 1] * inv),
+                        (__bf16)(o[db][4 * rg + 2] * inv), (__bf16)(o[db][4 * rg + 3] * inv)};
+      *reinterpret_cast<lds2*>(lds + lrow * kOutStr + 16 * rg + 8 * lh) =
+          __builtin_bit_cast(lds2, v);
+    }
+    // LDS keeps a wave's accesses in order; this keeps the compiler to it
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const lds4 v = *reinterpret_cast<const lds4*>(lds + (r4 + 16 * h) * kOutStr + 16 * c4);
+      if (r4 + 16 * h < n) *reinterpret_cast<lds4*>(out + off[h] + 32 * db + 8 * c4) = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }

@@ -533,23 +533,20 @@ __global__ __launch_bounds__(256 * R * KS, 3) void attn_fp8_kernel(
   for (int i = 0; i < HPW; ++i) {
     if (!wave_active[i]) continue;
     const float lt = KS > 1 ? l[i] : l[i] + __shfl_xor(l[i], 32);
-    if (rbase + lrow >= it.n_rows) continue;
-    const float inv = 1.0f / lt;
+    const int n_mine = min(32, it.n_rows - rbase);   // this row block's rows
+    if (n_mine <= 0) continue;
     const int hq = g * G + (G >= 4 ? it.head0 : 0) + w + 4 * i;
-    uint16_t* op = out + ((int64_t)row * n_q_heads + hq) * kD;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int d0 = 32 * db + 8 * rg + 4 * lh;
-        uint2 v;
-        v.x = pack_bf16x2(o[i][db][4 * rg] * inv, o[i][db][4 * rg + 1] * inv);
-        v.y = pack_bf16x2(o[i][db][4 * rg + 2] * inv, o[i][db][4 * rg + 3] * inv);
-        *reinterpret_cast<uint2*>(op + d0) = v;
-      }
     // lse (natural log) = (m + log2 l) * ln 2 with m in log2 units
-    if (lse && lh == 0)
+    if (lse && lh == 0 && lrow < n_mine)
       lse[(int64_t)row * n_q_heads + hq] = (m[i] + log2f(lt)) * 0.69314718055994531f;
+    // (the cos/sin rows' LDS is free: every wave is past a later barrier)
+    static_assert(4 * R * kOutLds <= (int)sizeof(rl), "outputs go through it");
+    store_out(o[i], 1.0f / lt, reinterpret_cast<uint8_t*>(&rl[0][0][0]) + (4 * rb + w) * kOutLds,
+              lane, n_mine, out, [&](int r) -> int64_t {
+                const int cr =
+                    it.crow0 >= 0 ? it.crow0 + rbase + r : arows[it.row0 + rbase + r].row;
+                return ((int64_t)cr * n_q_heads + hq) * kD;
+              });
   }
 }
 
