@@ -794,13 +794,19 @@ int ilog2(int x) {
 //   lse = log sum_c exp(lse_c),   o = sum_c exp(lse_c - lse) o_c,
 // o rounded to bf16 once.
 //
-// Bound by reading the partial rows, which the split kernel has just left in
-// the caches.  Half a wave takes a (row, head): its 32 lanes read the 512
-// bytes of a partial row together and lane c % 32 holds the weight of range
-// c.  kMergeCut workgroups share a row block of a split item, so that a
-// launch of a few dozen row blocks still fills the chip.
-constexpr int kMergeCut = 8;
+// Bound by latency: the partial rows have just been left in the caches, and
+// a launch merges a few thousand of them.  Half a wave takes one (row, head):
+// its 32 lanes read the 512 bytes of a partial row together and lane c % 32
+// holds the weight of range c.  The first kMergeAhead rows and the log-sum-exps
+// are all asked for at once, so a pair costs the merge descriptor's latency
+// and one more.  kMergeCut workgroups share a row block of a split item.
+// (Before: two pairs a half-wave in turn, each waiting for its log-sum-exps
+// before its rows.  A layer of one RAG request with every chunk cached 53.2 ->
+// 48.8 us, of which the merge had 9.)
+constexpr int kMergeCut = 16;
 constexpr int kMergePairs = kTileRows * kSplitHeads / kMergeCut;   // (row, head)s each
+constexpr int kMergeAhead = 8;
+static_assert(kMergePairs == 8, "one a half-wave");
 
 __global__ __launch_bounds__(256) void attn_merge_kernel(
     const CombineDesc* __restrict__ cds, const AttnRow* __restrict__ arows,
@@ -808,45 +814,53 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(
     uint16_t* __restrict__ out, float* __restrict__ lse, int n_q_heads) {
   const CombineDesc cd = cds[blockIdx.x];
   const int lane = threadIdx.x & 31;
-  for (int i = threadIdx.x >> 5; i < kMergePairs; i += 8) {
-    const int pair = blockIdx.y * kMergePairs + i;
-    const int r = pair / kSplitHeads, hs = pair % kSplitHeads;
-    if (r >= cd.n_rows || hs >= cd.n_heads) continue;
-    auto slot_row = [&](int c) -> int64_t {
-      return ((int64_t)(cd.slot0 + c) * kTileRows + r) * kSplitHeads + hs;
-    };
-    auto range_lse = [&](int c) { return c < cd.n_slots ? split_lse[slot_row(c)] : -INFINITY; };
-    float mx = -INFINITY;
-    for (int c = lane; c < cd.n_slots; c += 32) mx = fmaxf(mx, range_lse(c));
+  const int pair = blockIdx.y * kMergePairs + (threadIdx.x >> 5);
+  const int r = pair / kSplitHeads, hs = pair % kSplitHeads;
+  if (r >= cd.n_rows || hs >= cd.n_heads) return;
+  auto slot_row = [&](int c) -> int64_t {
+    return ((int64_t)(cd.slot0 + c) * kTileRows + r) * kSplitHeads + hs;
+  };
+  auto part = [&](int c) {
+    return *reinterpret_cast<const float4*>(split_o + slot_row(c) * kD + 4 * lane);
+  };
+  auto range_lse = [&](int c) { return c < cd.n_slots ? split_lse[slot_row(c)] : -INFINITY; };
+  const float l0 = range_lse(lane);
+  const int row = arows[cd.row0 + r].row;
+  float4 ahead[kMergeAhead];   // past the last range: its row again, unused
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    float den = 0.0f;
-    for (int c = lane; c < cd.n_slots; c += 32) den += expf(range_lse(c) - mx);
+  for (int c = 0; c < kMergeAhead; ++c) ahead[c] = part(min(c, cd.n_slots - 1));
+  float mx = l0;
+  for (int c = lane + 32; c < cd.n_slots; c += 32) mx = fmaxf(mx, range_lse(c));
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
-    const float ltot = mx + logf(den);
-    float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int c0 = 0; c0 < cd.n_slots; c0 += 32) {
-      const int nc = min(32, cd.n_slots - c0);
-      const float wl = expf(range_lse(c0 + lane) - ltot);
-#pragma unroll 4
-      for (int c = 0; c < nc; ++c) {
-        const float wc = __shfl(wl, c, 32);
-        const float4 v =
-            *reinterpret_cast<const float4*>(split_o + slot_row(c0 + c) * kD + 4 * lane);
-        acc.x = fmaf(wc, v.x, acc.x);
-        acc.y = fmaf(wc, v.y, acc.y);
-        acc.z = fmaf(wc, v.z, acc.z);
-        acc.w = fmaf(wc, v.w, acc.w);
-      }
-    }
-    const int64_t orow = (int64_t)arows[cd.row0 + r].row * n_q_heads + cd.hq0 + hs;
-    uint2 v;
-    v.x = f32_to_bf16(acc.x) | (f32_to_bf16(acc.y) << 16);
-    v.y = f32_to_bf16(acc.z) | (f32_to_bf16(acc.w) << 16);
-    *reinterpret_cast<uint2*>(out + orow * kD + 4 * lane) = v;
-    if (lse && lane == 0) lse[orow] = ltot;
+  for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  float den = expf(l0 - mx);
+  for (int c = lane + 32; c < cd.n_slots; c += 32) den += expf(range_lse(c) - mx);
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
+  const float ltot = mx + logf(den);
+  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  auto add = [&](float wc, const float4& v) {
+    acc.x = fmaf(wc, v.x, acc.x);
+    acc.y = fmaf(wc, v.y, acc.y);
+    acc.z = fmaf(wc, v.z, acc.z);
+    acc.w = fmaf(wc, v.w, acc.w);
+  };
+  float wl = expf(l0 - ltot);
+#pragma unroll
+  for (int c = 0; c < kMergeAhead; ++c) {
+    const float wc = __shfl(wl, c, 32);
+    if (c < cd.n_slots) add(wc, ahead[c]);
   }
+  for (int c = kMergeAhead; c < cd.n_slots; ++c) {
+    if (c % 32 == 0) wl = expf(range_lse(c + lane) - ltot);
+    add(__shfl(wl, c % 32, 32), part(c));
+  }
+  const int64_t orow = (int64_t)row * n_q_heads + cd.hq0 + hs;
+  uint2 v;
+  v.x = f32_to_bf16(acc.x) | (f32_to_bf16(acc.y) << 16);
+  v.y = f32_to_bf16(acc.z) | (f32_to_bf16(acc.w) << 16);
+  *reinterpret_cast<uint2*>(out + orow * kD + 4 * lane) = v;
+  if (lse && lane == 0) lse[orow] = ltot;
 }
 
 }  // namespace
