@@ -233,10 +233,11 @@ tsr_status tsr_plan_create(const tsr_model* model, const tsr_request* reqs,
  *             TSR_SCOPE_LOCAL the rows after the units attend to the whole
  *             prompt while most rows attend within a short unit.
  *               0   automatic: for items of one row block, S = the
- *                   launch's mean key tiles per compute unit (256 units,
- *                   24 tiles at least), or 65 % of that in launches of
- *                   fewer than 768 items, so only items that would outlast
- *                   the rest of the launch are split; items of three row
+ *                   launch's mean key tiles per compute unit (256 units),
+ *                   or 65 % of that in launches of fewer than 768 items,
+ *                   8 tiles at least, so only items that would outlast the
+ *                   rest of the launch are split, and none where no item
+ *                   spans more than 24 tiles; items of three row
  *                   blocks are not split; never for tsr_plan_create_static;
  *               >0  S = split_tiles;
  *               -1  never split.

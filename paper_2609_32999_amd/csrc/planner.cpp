@@ -516,9 +516,13 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
     auto tiles_of = [](const AttnItem& a) -> int64_t {
       return (a.kv_len + kMfmaKeys - 1) / kMfmaKeys - a.kv_lo / kMfmaKeys;
     };
-    int64_t total = 0;
-    for (const Item& x : items) total += tiles_of(x.it);
+    int64_t total = 0, longest = 0;
+    for (const Item& x : items) {
+      total += tiles_of(x.it);
+      longest = std::max(longest, tiles_of(x.it));
+    }
     int64_t S = split_threshold(total);
+    if (split_tiles == 0 && longest <= kMinSplitLongest) S = longest;   // none
     auto slots_for = [&](int64_t lim) {
       int64_t n = 0;
       for (const Item& x : items) {

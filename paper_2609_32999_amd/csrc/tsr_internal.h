@@ -156,15 +156,21 @@ constexpr int kSplitHeads = 4;
 // fill the units whose items end first, and is capped at kSplitSharePct per
 // cent of that: one RAG request (440 items, mean 142 tiles) ran 137 us capped
 // at its mean and 110 at anything from 84 to 112 tiles; below 80 the ranges'
-// partial rows cost more than they spread (119 us at 64, 131 at 24).  With
-// every chunk cached (64 items, mean 21) 24 tiles gave 37 us, 32 gave 40 and
-// 16 gave 38.  (Capping larger launches at the mean per workgroup slot did
+// partial rows cost more than they spread (119 us at 64, 131 at 24).
+// kMinSplitTiles: below 8 tiles a range's own start costs what it saves.  With
+// every chunk cached (64 items, mean 21) ranges of 24 tiles ran 34.7 us and the
+// 13 of this rule 33.2; four chunks (40 items, mean 6) 26.6 and 18.4 at 8, 17.9
+// at 6; a 28-tile prompt (72 items) 27.5 and 20.3 at 8, 21.9 at 6; 432 items of
+// up to 28 tiles 41.7 and 40.1.  A launch whose longest item has at most
+// kMinSplitLongest tiles stays whole: its plan keeps no buffer that calls on
+// concurrent streams would share.  (Capping larger launches at the mean per workgroup slot did
 // not shorten the RAG-8B batch under the LOCAL scope: that launch is bound
 // by its total work, not by its longest item.)
 constexpr int kSplitSlots = 256;
 constexpr int kFullLaunchItems = 3 * kNumCus;
 constexpr int kSplitSharePct = 65;
-constexpr int kMinSplitTiles = 24;
+constexpr int kMinSplitTiles = 8;
+constexpr int kMinSplitLongest = 24;
 // At most this many split buffer slots (64 KiB each at head_dim 128).
 constexpr int kMaxSplitSlots = 4096;
 
