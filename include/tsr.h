@@ -26,7 +26,10 @@
  *     TSR_OK is returned, nothing is enqueued, and tsr_last_error() (a
  *     thread-local string) says why.
  *   - Thread safety: plans are immutable after creation and may be used
- *     from several threads and streams at once.
+ *     from several threads and streams at once; the exceptions are plans
+ *     with split items (tsr_plan_num_attn_splits > 0), whose attention
+ *     calls must not overlap (split_tiles below), and the area static
+ *     plans share.
  *
  * KV page layout (pool and request pages alike), one layer:
  *     [n_pages][n_kv_heads][page_size][head_dim]   (head-major within a page)
@@ -232,13 +235,14 @@ tsr_status tsr_plan_create(const tsr_model* model, const tsr_request* reqs,
  *             launch lasts at least as long as its longest item: under
  *             TSR_SCOPE_LOCAL the rows after the units attend to the whole
  *             prompt while most rows attend within a short unit.
- *               0   automatic: for items of one row block, S = the
+ *               0   automatic: for items of one row block, if one of
+ *                   them spans more than 32 tiles and more than the
  *                   launch's mean key tiles per compute unit (256 units),
- *                   or 65 % of that in launches of fewer than 768 items,
- *                   8 tiles at least, so only items that would outlast the
- *                   rest of the launch are split, and none where no item
- *                   spans more than 24 tiles; items of three row
- *                   blocks are not split; never for tsr_plan_create_static;
+ *                   with its smallest position past its first tile: S =
+ *                   that mean, or 65 % of it in launches of fewer than 768
+ *                   items, 8 tiles at least; no other launch is split, nor
+ *                   are items of three row blocks; never for
+ *                   tsr_plan_create_static;
  *               >0  S = split_tiles;
  *               -1  never split.
  *             A plan with split items writes that buffer on every

@@ -455,12 +455,6 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   // three / one row blocks.
   p->row_blocks = 1;
   const bool bf16_kv = m.act_dtype == TSR_BF16 && m.kv_dtype == TSR_BF16;
-  auto split_threshold = [&](int64_t total_tiles) -> int64_t {
-    if (split_tiles > 0) return split_tiles;
-    int64_t mean = (total_tiles + kSplitSlots - 1) / kSplitSlots;
-    if ((int64_t)items.size() < kFullLaunchItems) mean = mean * kSplitSharePct / 100;
-    return std::max<int64_t>(kMinSplitTiles, mean);
-  };
   const bool mfma = m.act_dtype == TSR_BF16 &&
                     (m.kv_dtype == TSR_BF16 || m.kv_dtype == TSR_E4M3);
   if (bf16_kv && attn_kernel == 1) {
@@ -521,8 +515,17 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
       total += tiles_of(x.it);
       longest = std::max(longest, tiles_of(x.it));
     }
-    int64_t S = split_threshold(total);
-    if (split_tiles == 0 && longest <= kMinSplitLongest) S = longest;   // none
+    int64_t S = split_tiles;
+    if (split_tiles == 0) {
+      const int64_t mean = (total + kSplitSlots - 1) / kSplitSlots;
+      const bool any = std::any_of(items.begin(), items.end(), [&](const Item& x) {
+        return tiles_of(x.it) > std::max<int64_t>(kWholeTiles, mean) &&
+               x.it.min_pos / kMfmaKeys > x.it.kv_lo / kMfmaKeys;
+      });
+      const bool few_items = (int64_t)items.size() < kFullLaunchItems;
+      S = any ? std::max<int64_t>(kMinSplitTiles, few_items ? mean * kSplitSharePct / 100 : mean)
+              : longest;   // none split
+    }
     auto slots_for = [&](int64_t lim) {
       int64_t n = 0;
       for (const Item& x : items) {

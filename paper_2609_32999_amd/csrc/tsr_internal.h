@@ -158,19 +158,22 @@ constexpr int kSplitHeads = 4;
 // at its mean and 110 at anything from 84 to 112 tiles; below 80 the ranges'
 // partial rows cost more than they spread (119 us at 64, 131 at 24).
 // kMinSplitTiles: below 8 tiles a range's own start costs what it saves.  With
-// every chunk cached (64 items, mean 21) ranges of 24 tiles ran 34.7 us and the
-// 13 of this rule 33.2; four chunks (40 items, mean 6) 26.6 and 18.4 at 8, 17.9
-// at 6; a 28-tile prompt (72 items) 27.5 and 20.3 at 8, 21.9 at 6; 432 items of
-// up to 28 tiles 41.7 and 40.1.  A launch whose longest item has at most
-// kMinSplitLongest tiles stays whole: its plan keeps no buffer that calls on
-// concurrent streams would share.  (Capping larger launches at the mean per workgroup slot did
-// not shorten the RAG-8B batch under the LOCAL scope: that launch is bound
-// by its total work, not by its longest item.)
+// every chunk cached (64 items, mean 19) ranges of 24 tiles ran 34.7 us and
+// the 12 of this rule 33.2; four chunks (40 items, mean 6) 26.6 and 18.4 at 8,
+// 17.9 at 6.
+// A launch is split at all only if one of its items spans more than both its
+// mean and kWholeTiles, and some of that item's rows start past its first key
+// tile; else it stays whole, faster split or not (a 28-tile prompt of 72 items
+// would take 20 us instead of 27, 432 items of up to 28 tiles 40 instead of
+// 34): its plan keeps no buffer that calls on concurrent streams would share.
+// (Capping larger launches at the mean per workgroup slot did not shorten the
+// RAG-8B batch under the LOCAL scope: that launch is bound by its total work,
+// not by its longest item.)
 constexpr int kSplitSlots = 256;
 constexpr int kFullLaunchItems = 3 * kNumCus;
 constexpr int kSplitSharePct = 65;
 constexpr int kMinSplitTiles = 8;
-constexpr int kMinSplitLongest = 24;
+constexpr int kWholeTiles = 32;
 // At most this many split buffer slots (64 KiB each at head_dim 128).
 constexpr int kMaxSplitSlots = 4096;
 

@@ -464,3 +464,66 @@ def test_split_automatic_threshold():
     assert one.attn_rows_per_item == 32 and one.num_attn_splits > 0
     _, (glob,), _ = _split_plans("rag8b", "global", 0)
     assert glob.attn_rows_per_item == 96 and glob.num_attn_splits == 0
+
+
+def _text_and_windows(units, window, text, n_req=1):
+    """Requests of `units` cached units of 512 tokens with `window` leading
+    tokens recomputed each, then `text` text tokens."""
+    reqs, pool, page = [], 0, 0
+    for r in range(n_req):
+        us = []
+        for i in range(units):
+            us.append(NS(unit_id=r * units + i, n_tokens=512, position=512 * i, residency=1,
+                         n_recompute=window, retain=0,
+                         pool_pages=np.arange(pool, pool + 32, dtype=np.int32)))
+            pool += 32
+        n = 512 * units + text
+        pages = -(-n // 16)
+        reqs.append(NS(prompt_len=n, units=us, text_segs=[(512 * units, text)],
+                       block_table=np.arange(page, page + pages, dtype=np.int32)))
+        page += pages
+    return reqs, max(pool, 1), page
+
+
+# (cached units, window, text tokens, requests, query heads), and whether the
+# plan keeps a split buffer
+_AUTO_SPLITS = [
+    (0, 0, 832, 1, 32, False), (0, 0, 960, 1, 32, False), (0, 0, 1024, 1, 32, False),
+    (0, 0, 1025, 1, 32, True),            # 33 tiles, mean 18 a unit
+    (0, 0, 960, 2, 32, False), (0, 0, 960, 4, 32, False), (0, 0, 896, 6, 32, False),
+    (0, 0, 1024, 1, 64, False), (0, 0, 1025, 1, 64, False),   # mean 36
+    (0, 0, 1025, 1, 8, True),
+    (0, 0, 2080, 1, 32, False),           # 65 tiles, mean 68
+    (0, 0, 2400, 1, 32, False),           # 75 tiles, mean 90: more than 65 % of it
+    (1, 32, 1024, 1, 32, True),
+    # the whole launch one item of windows far apart, the first at the start
+    (10, 1, 16, 1, 32, False),
+    (10, 1, 16, 2, 32, False),
+    (10, 16, 32, 1, 32, True),            # later items start further on
+]
+
+
+@pytest.mark.parametrize("units,window,text,n_req,hq,split", _AUTO_SPLITS)
+def test_split_automatic_keeps_plans_whole(units, window, text, n_req, hq, split):
+    """Calls of one plan on concurrent streams share its split buffer, so the
+    automatic rule gives one only to launches with an item past both 32 key
+    tiles and the mean per compute unit, whose smallest position lies past
+    its first tile; every other plan's workspace is that of -1."""
+    reqs, n_pool, n_pages = _text_and_windows(units, window, text, n_req)
+    m = P.make_model(n_q_heads=hq, n_kv_heads=8, head_dim=128, page_size=16, kv_dtype="bf16",
+                     act_dtype="bf16", rope_theta=5e5, max_position=8192)
+    batch = P.RequestBatch(reqs)
+    plan = P.tsr_plan_create(m, batch, n_pool, n_pages, attn_kernel=4)
+    ws = [P.tsr_plan_workspace_size(m, batch, n_pool, n_pages, attn_kernel=4, split_tiles=s)
+          for s in (0, -1)]
+    # the rule, from the rows
+    pos, req = plan.compute_positions()
+    per = 8 * max(1, hq // 8 // 4)
+    items = []
+    for r in range(n_req):
+        p = pos[req == r]
+        items += [(p[a], p[min(a + 32, len(p)) - 1] // 32 + 1) for a in range(0, len(p), 32)]
+    mean = -(-sum(t for _, t in items) * per // 256)
+    assert split == any(t > max(32, mean) and lo >= 32 for lo, t in items)
+    assert (plan.num_attn_splits > 0) == split
+    assert (ws[0] > ws[1]) == split
