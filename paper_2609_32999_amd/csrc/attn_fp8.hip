@@ -496,8 +496,10 @@ __global__ __launch_bounds__(256 * R * KS, 3) void attn_fp8_kernel(
     for (int i = 0; i < KS; ++i) mx = fmaxf(mx, ml[i][w][lrow][0]);
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const float mi = ml[i][w][lrow][0];
-      lt += mi == -INFINITY ? 0.0f : ml[i][w][lrow][1] * __builtin_amdgcn_exp2f(mi - mx);
+      // a group that saw none of the row's keys adds nothing; one whose scores
+      // are all NaN has no maximum either, but its sum is NaN
+      const float mi = ml[i][w][lrow][0], li = ml[i][w][lrow][1];
+      lt += mi == -INFINITY && li == 0.0f ? 0.0f : li * __builtin_amdgcn_exp2f(mi - mx);
     }
     const float f = m[0] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m[0] - mx);
     m[0] = mx;
