@@ -756,9 +756,12 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
   if (it.part_slot >= 0) {
     // one key range of a split item: normalized rows and log-sum-exp in
     // fp32 to this row block's slot, merged by attn_merge_kernel; a row
-    // that sees no key of the range weighs nothing there (0, -inf)
+    // that sees no key of the range weighs nothing there (0, -inf).  (A row
+    // whose scores in it are all NaN has no maximum either, but its sum is
+    // NaN.)
     if (lrow >= n_mine) return;
-    if (m == -INFINITY) inv = 0.0f;
+    const bool none = m == -INFINITY && lt == 0.0f;
+    if (none) inv = 0.0f;
     const int64_t slot = it.part_slot + (int64_t)rb * it.n_parts;
     const int64_t sr = (slot * kTileRows + lrow) * kSplitHeads + w;
     float* po = split_o + sr * kD;
@@ -769,7 +772,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
         *reinterpret_cast<float4*>(po + 32 * db + 8 * rg + 4 * lh) =
             make_float4(o[db][4 * rg] * inv, o[db][4 * rg + 1] * inv,
                         o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-    if (lh == 0) split_lse[sr] = m == -INFINITY ? -INFINITY : m * scale + logf(lt);
+    if (lh == 0) split_lse[sr] = none ? -INFINITY : m * scale + logf(lt);
     return;
   }
   const int hq = g * G + (G >= 4 ? it.head0 : 0) + w;

@@ -40,6 +40,18 @@ def _check_nan(got, rows):
         assert torch.isnan(t[rows].float()).all()
 
 
+def _check_finite(got, rows):
+    for t in got:
+        assert torch.isfinite(t[rows].float()).all()
+
+
+def _bf16(kernel, split):
+    wl = workloads.make_workload(workloads.get_config("small_bf16"))
+    run = GpuRun(wl, attn_kernel=kernel, split_tiles=split)
+    assert (run.plan.num_attn_splits > 0) == (split > 0)
+    return run
+
+
 def _fp8():
     cfg = workloads.get_config("small_fp8")
     wl = workloads.make_workload(cfg.with_(
@@ -49,6 +61,32 @@ def _fp8():
     run = GpuRun(wl, attn_kernel=4)
     assert run.wl.requests[0].prompt_len >= 1024
     return run
+
+
+_PLANS = [(4, -1), (3, -1), (4, 2), (3, 2), (4, 5)]
+
+
+@pytest.mark.parametrize("kernel,split", _PLANS)
+def test_bf16_nan_query(kernel, split):
+    run = _bf16(kernel, split)
+    row = int(run.rows_of(0)[-1])
+    q = run.q.clone()
+    q[row] = float("nan")
+    got = _attn(run, q)
+    _check_nan(got, [row])
+    _check_finite(got, [r for r in range(len(run.pos)) if r != row])
+
+
+@pytest.mark.parametrize("kernel,split", _PLANS)
+def test_bf16_nan_keys(kernel, split):
+    """Keys 32 .. 319 of request 0: at least one whole range of 2 or 5 tiles."""
+    run = _bf16(kernel, split)
+    assert run.wl.requests[0].prompt_len > 320
+    run.sess.req_k[0][_pages(run, 32, 320)] = float("nan")
+    got = _attn(run, run.q)
+    rows = run.rows_of(0)
+    _check_nan(got, rows[run.pos[rows] >= 32])
+    _check_finite(got, np.setdiff1d(np.arange(len(run.pos)), rows[run.pos[rows] >= 32]))
 
 
 @pytest.mark.parametrize("first", [0, 1, 2])
