@@ -369,7 +369,7 @@ def attention_flops(plan, m):
 def attention_kernel_name(plan, m):
     G = m.n_q_heads // m.n_kv_heads
     if m.kv_dtype == "e4m3":
-        return f"attn_fp8_kernel<{G}, {plan.attn_rows_per_item // 32}>"
+        return f"attn_fp8_kernel<{G}, {plan.attn_rows_per_item // 32}, {plan.attn_wave_groups}>"
     if plan.attn_rows_per_item == 64:       # the pipelined kernel
         return f"attn_pipe_kernel<{G}, {str(plan.alias_v).lower()}>"
     return (f"attn_mfma_kernel<{G}, {str(plan.alias_v).lower()}, "

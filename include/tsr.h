@@ -335,6 +335,9 @@ int32_t tsr_plan_attn_rows_per_item(const tsr_plan* plan);
 /* Number of attention items whose key range was split (split_tiles), each
  * merged by the second kernel; 0 when none; -1 for a null plan. */
 int32_t tsr_plan_num_attn_splits(const tsr_plan* plan);
+/* Wave groups that share the key tiles of an attention item: 3 in launches
+ * of the e4m3 kernel that they shorten, else 1; -1 for a null plan. */
+int32_t tsr_plan_attn_wave_groups(const tsr_plan* plan);
 
 /* The attention items in two parts, so that attention can start while the
  * cached states are still on their way (Section 5.3: cache hits transfer

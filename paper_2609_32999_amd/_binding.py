@@ -33,7 +33,7 @@ TSR_ATTN_ALL, TSR_ATTN_BEFORE_COMPOSE, TSR_ATTN_AFTER_COMPOSE = 0, 1, 2
 EXPORTS = (
     "tsr_abi_version", "tsr_last_error", "tsr_rope_table_bytes",
     "tsr_rope_table_init", "tsr_plan_workspace_size", "tsr_plan_workspace_size_ex",
-    "tsr_plan_create", "tsr_plan_num_attn_splits",
+    "tsr_plan_create", "tsr_plan_num_attn_splits", "tsr_plan_attn_wave_groups",
     "tsr_plan_num_compute_tokens", "tsr_plan_num_gather_tokens",
     "tsr_plan_num_retain_tokens", "tsr_plan_num_attn_items", "tsr_plan_attn_rows_per_item",
     "tsr_plan_num_attn_items_part", "tsr_attn_part", "tsr_plan_create_ex", "tsr_plan_create_static",
@@ -133,6 +133,7 @@ def lib():
             "tsr_plan_num_aliased_pages": (c_int32, [P]),
             "tsr_plan_num_aliased_k_pages": (c_int32, [P]),
             "tsr_plan_num_attn_splits": (c_int32, [P]),
+            "tsr_plan_attn_wave_groups": (c_int32, [P]),
             "tsr_plan_workspace_size_ex": (c_size_t, [POINTER(tsr_model), POINTER(tsr_request),
                                                       c_int32, c_int32, c_int32,
                                                       POINTER(tsr_plan_options)]),
@@ -338,6 +339,10 @@ class Plan:
     @property
     def num_attn_splits(self) -> int:
         return lib().tsr_plan_num_attn_splits(self.handle)
+
+    @property
+    def attn_wave_groups(self) -> int:
+        return lib().tsr_plan_attn_wave_groups(self.handle)
 
     def compute_positions(self):
         T = self.num_compute_tokens

@@ -301,6 +301,7 @@ int32_t tsr_plan_attn_rows_per_item(const tsr_plan* p) {
 }
 int32_t tsr_plan_num_aliased_pages(const tsr_plan* p) { return p ? p->n_aliased : -1; }
 int32_t tsr_plan_num_attn_splits(const tsr_plan* p) { return p ? p->n_split_items : -1; }
+int32_t tsr_plan_attn_wave_groups(const tsr_plan* p) { return p ? p->wave_groups : -1; }
 int32_t tsr_plan_num_aliased_k_pages(const tsr_plan* p) { return p ? p->n_aliased_k : -1; }
 
 int32_t tsr_plan_num_attn_items_part(const tsr_plan* p, int32_t part) {

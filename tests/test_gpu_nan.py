@@ -59,7 +59,7 @@ def _fp8():
         residency_pattern=(0, 1, 0, 1), unit_order=((0, 1, 2, 3),), instruction_tokens=16,
         query_tokens=17, extra={}))
     run = GpuRun(wl, attn_kernel=4)
-    assert run.wl.requests[0].prompt_len >= 1024
+    assert run.plan.attn_wave_groups == 3
     return run
 
 
