@@ -14,6 +14,7 @@
 //   * attention items -- tiles of consecutive computed rows x KV heads, in an
 //                       XCD-aware, longest-first launch order.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <numeric>
@@ -475,14 +476,6 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   } else {
     build_items(1);
   }
-  // An e4m3 launch of fewer one-row-block items than the chip holds at once
-  // lasts as long as its longest item, whose key tiles go to kWaveGroups wave
-  // groups then, if it has enough of them.
-  const bool few = (int64_t)items.size() < kFullLaunchItems;
-  p->wave_groups = mfma && !bf16_kv && p->row_blocks == 1 && few &&
-                           max_blocks >= 2 * kMinGroupTiles
-                       ? kWaveGroups
-                       : 1;
   p->rows_grouped = !std::is_sorted(ord.begin(), ord.end());
   std::vector<AttnRow> attn_rows((size_t)T);
   for (int32_t i = 0; i < T; ++i) attn_rows[i] = AttnRow{ord[i], p->row_pos[ord[i]]};
@@ -637,6 +630,26 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   };
   std::vector<AttnItem> order = schedule(-1);
   std::vector<AttnItem> order_part[2] = {schedule(0), schedule(1)};
+  // Wave groups of a one-row-block e4m3 launch of fewer items than the chip
+  // holds at once: whether the launch is shorter with a workgroup per unit
+  // whose groups share an item's key tiles, from the order it is issued in.
+  p->wave_groups = 1;
+  if (mfma && !bf16_kv && p->row_blocks == 1 && (int64_t)items.size() < kFullLaunchItems &&
+      max_blocks >= 2 * kMinGroupTiles) {
+    int64_t last = 0;   // group steps until the last unit is done
+    for (int b = 0; b < kNumXcd; ++b) {
+      std::array<int64_t, kNumCus / kNumXcd> unit{};
+      for (size_t i = b; i < order.size(); i += kNumXcd) {
+        const AttnItem& a = order[i];
+        if (a.n_rows == 0) continue;
+        const int64_t tiles = (a.kv_len + kMfmaKeys - 1) / kMfmaKeys - a.kv_lo / kMfmaKeys;
+        int64_t& u = *std::min_element(unit.begin(), unit.end());
+        u += kGroupItemSteps + (tiles + kWaveGroups - 1) / kWaveGroups;
+        last = std::max(last, u);
+      }
+    }
+    if (kGroupStepPct * last <= 100 * (max_blocks / 2 + kItemTiles)) p->wave_groups = kWaveGroups;
+  }
   // first key tile's page ids, from the block table the kernels read for K
   {
     const std::vector<int32_t>& kt = alias_k ? kbts : bts;

@@ -27,16 +27,27 @@ constexpr int kTileRows = 32;
 // grouping) the two were level.
 constexpr int kMaxRowBlocks = 3;
 constexpr double kMinGroupedRowBlockUse = 0.6;
-// Wave groups that share the key tiles of a one-row-block e4m3 item, in
-// launches of fewer than kFullLaunchItems items whose longest spans at least
-// kMinGroupTiles key tiles.  One fp8 RAG request (464 items, up to 260 tiles)
-// 202 -> 133 us, with every chunk cached (88 items) 186 -> 119, four chunks
-// (168 items, 67 tiles) 56 -> 42, 648 items 213 -> 199; four requests of 17
-// tiles 20 -> 26.
-constexpr int kWaveGroups = 3;
-constexpr int kMinGroupTiles = 32;
 // Compute units of the GPU (MI355X).
 constexpr int kNumCus = 256;
+// Wave groups that share the key tiles of a one-row-block e4m3 item, in
+// launches of fewer than kFullLaunchItems items whose longest spans at least
+// kMinGroupTiles key tiles (four requests of 17 tiles ran 20 us without and 26
+// with), where they shorten the launch: a grouped workgroup has a unit to
+// itself, so items queue for the units.  With groups a launch lasts 1.43 us
+// for each step of the unit that ends last, an item taking a step for every
+// kWaveGroups tiles and kGroupItemSteps to start and merge (a fit of 121
+// random launches, 6 % rms); without, 0.75 us a tile of the longest item and
+// kItemTiles to start it, the others run beside it.  On 160 other launches the
+// rule's choice was within 5 % of the better one.  With groups, one fp8 RAG
+// request (464 items, up to 260 tiles) 202 -> 133 us, with every chunk cached
+// (88 items) 186 -> 119, four chunks (168 items, 67 tiles) 56 -> 42; against
+// it, 560 items of up to 35 tiles 35 us and 50 with groups, 656 of up to 50
+// tiles 50 and 61.
+constexpr int kWaveGroups = 3;
+constexpr int kMinGroupTiles = 32;
+constexpr int kGroupItemSteps = 6;
+constexpr int kItemTiles = 5;
+constexpr int kGroupStepPct = 190;   // a group step in lone tiles
 // Attention launches with at least this many (request, KV head) groups per
 // XCD bin issue each bin group by group within thirds of the cost range.
 // Measured: Agent-8B (32 groups per bin) 4.6 % faster; fp8 RAG (16) 3 % and

@@ -527,3 +527,33 @@ def test_split_automatic_keeps_plans_whole(units, window, text, n_req, hq, split
     assert split == any(t > max(32, mean) and lo >= 32 for lo, t in items)
     assert (plan.num_attn_splits > 0) == split
     assert (ws[0] > ws[1]) == split
+
+
+# (cached units of 512, window, text tokens, requests, heads): wave groups.
+# Tiles and items of each are those of _text_and_windows.
+_WAVE_GROUPS = [
+    (0, 0, 992, 1, 32, 8, 1), (0, 0, 1024, 1, 32, 8, 3),     # 31 and 32 tiles
+    (0, 0, 2048, 1, 32, 8, 3), (0, 0, 2400, 1, 32, 8, 1),    # two items a unit, and up to three
+    (0, 0, 1024, 2, 32, 8, 1), (0, 0, 1120, 2, 32, 8, 1),
+    (0, 0, 1024, 1, 64, 8, 1),
+    (0, 0, 1024, 1, 32, 4, 1),      # 256 items, on the units of four XCDs
+    (0, 0, 1024, 1, 4, 4, 3),       # 128, one query head a KV head
+    (10, 16, 32, 1, 32, 8, 3), (10, 16, 32, 8, 32, 8, 3),
+    (48, 16, 32, 3, 32, 8, 3), (48, 16, 32, 4, 32, 8, 1),    # 600 and 800 items
+]
+
+
+@pytest.mark.parametrize("units,window,text,n_req,hq,hkv,groups", _WAVE_GROUPS)
+def test_wave_group_rule(units, window, text, n_req, hq, hkv, groups):
+    """Which e4m3 launches deal an item's key tiles to three wave groups:
+    one-row-block items, fewer than 768 of them, the longest of 32 tiles or
+    more, and the launch shorter with one workgroup a unit."""
+    reqs, n_pool, n_pages = _text_and_windows(units, window, text, n_req)
+    m = dict(n_q_heads=hq, n_kv_heads=hkv, head_dim=128, page_size=16, act_dtype="bf16",
+             rope_theta=5e5, max_position=65536)
+    mk = lambda dt, **kw: P.tsr_plan_create(P.make_model(kv_dtype=dt, **m),
+                                            P.RequestBatch(reqs), n_pool, n_pages, **kw)
+    plan = mk("e4m3", attn_kernel=4)
+    assert plan.attn_wave_groups == groups, plan.num_attn_items
+    assert mk("e4m3", attn_kernel=3).attn_wave_groups == 1
+    assert mk("bf16", attn_kernel=4).attn_wave_groups == 1
