@@ -240,9 +240,10 @@ tsr_status tsr_plan_create(const tsr_model* model, const tsr_request* reqs,
  *                   launch's mean key tiles per compute unit (256 units),
  *                   with its smallest position past its first tile: S =
  *                   that mean, or 65 % of it in launches of fewer than 768
- *                   items, 8 tiles at least; no other launch is split, nor
- *                   are items of three row blocks; never for
- *                   tsr_plan_create_static;
+ *                   items, 8 tiles at least (the mean and 32 tiles where
+ *                   fewer requests x KV heads than XCDs keep few units
+ *                   busy); no other launch is split, nor are items of three
+ *                   row blocks; never for tsr_plan_create_static;
  *               >0  S = split_tiles;
  *               -1  never split.
  *             A plan with split items writes that buffer on every

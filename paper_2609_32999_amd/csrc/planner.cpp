@@ -515,9 +515,15 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
         return tiles_of(x.it) > std::max<int64_t>(kWholeTiles, mean) &&
                x.it.min_pos / kMfmaKeys > x.it.kv_lo / kMfmaKeys;
       });
-      const bool few_items = (int64_t)items.size() < kFullLaunchItems;
-      S = any ? std::max<int64_t>(kMinSplitTiles, few_items ? mean * kSplitSharePct / 100 : mean)
-              : longest;   // none split
+      const int64_t groups = (int64_t)n_req * Hkv;
+      if (!any)
+        S = longest;   // none split
+      else if (groups < kNumXcd && total > kFewGroupTiles * (kNumCus / kNumXcd) * groups)
+        S = std::max<int64_t>(kWholeTiles, mean);
+      else if ((int64_t)items.size() < kFullLaunchItems)
+        S = std::max<int64_t>(kMinSplitTiles, mean * kSplitSharePct / 100);
+      else
+        S = std::max<int64_t>(kMinSplitTiles, mean);
     }
     auto slots_for = [&](int64_t lim) {
       int64_t n = 0;

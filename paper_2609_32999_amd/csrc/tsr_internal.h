@@ -172,6 +172,14 @@ constexpr int kSplitHeads = 4;
 // every chunk cached (64 items, mean 19) ranges of 24 tiles ran 34.7 us and
 // the 12 of this rule 33.2; four chunks (40 items, mean 6) 26.6 and 18.4 at 8,
 // 17.9 at 6.
+// A (request, KV head) group runs on one XCD, so launches of fewer groups than
+// XCDs leave units idle, and the others fill up sooner than the mean says: with
+// more than kFewGroupTiles tiles on each, finer ranges queue there.  Such
+// launches are capped at the mean, kWholeTiles at least: 104 items on 32 units
+// of 74 tiles each 54.8 us (78.3 at 8 tiles), 152 on 128 units of 49 tiles 48.5
+// (57.8 at 16), 312 on 128 units of 95 tiles 75.9 (89.8 at 31); at 15 tiles or
+// less the finer ranges win by up to 2 x (64 items, 9 tiles a unit: 32.4 and
+// 19.1 us).
 // A launch is split at all only if one of its items spans more than both its
 // mean and kWholeTiles, and some of that item's rows start past its first key
 // tile; else it stays whole, faster split or not (a 28-tile prompt of 72 items
@@ -185,6 +193,7 @@ constexpr int kFullLaunchItems = 3 * kNumCus;
 constexpr int kSplitSharePct = 65;
 constexpr int kMinSplitTiles = 8;
 constexpr int kWholeTiles = 32;
+constexpr int kFewGroupTiles = 16;
 // At most this many split buffer slots (64 KiB each at head_dim 128).
 constexpr int kMaxSplitSlots = 4096;
 

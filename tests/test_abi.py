@@ -557,3 +557,36 @@ def test_wave_group_rule(units, window, text, n_req, hq, hkv, groups):
     assert plan.attn_wave_groups == groups, plan.num_attn_items
     assert mk("e4m3", attn_kernel=3).attn_wave_groups == 1
     assert mk("bf16", attn_kernel=4).attn_wave_groups == 1
+
+
+@pytest.mark.parametrize("units,window,text,n_req,hq,hkv", [
+    (0, 0, 2048, 1, 8, 1), (10, 16, 600, 1, 32, 4), (10, 16, 32, 1, 8, 1), (10, 16, 32, 3, 16, 2),
+    (10, 16, 32, 2, 32, 4), (10, 16, 32, 1, 32, 8), (10, 32, 900, 1, 32, 8),
+    (10, 32, 300, 1, 32, 8), (10, 16, 32, 1, 4, 2),
+])
+def test_split_automatic_range_length(units, window, text, n_req, hq, hkv):
+    """Ranges of a launch the automatic rule splits: the mean per compute
+    unit, 65 % of it below 768 items, 8 tiles at least; launches of fewer
+    (request, KV head) groups than XCDs whose units hold more than 16 tiles
+    each: the mean, 32 at least."""
+    reqs, n_pool, n_pages = _text_and_windows(units, window, text, n_req)
+    m = P.make_model(n_q_heads=hq, n_kv_heads=hkv, head_dim=128, page_size=16, kv_dtype="bf16",
+                     act_dtype="bf16", rope_theta=5e5, max_position=8192)
+    mk = lambda s: P.tsr_plan_create(m, P.RequestBatch(reqs), n_pool, n_pages, attn_kernel=4,
+                                     split_tiles=s)
+    plan = mk(0)
+    pos, req = plan.compute_positions()
+    per = hkv * max(1, hq // hkv // 4)
+    tiles = []
+    for r in range(n_req):
+        p = pos[req == r]
+        tiles += [p[min(a + 32, len(p)) - 1] // 32 + 1 for a in range(0, len(p), 32)]
+    total, groups = sum(tiles) * per, n_req * hkv
+    mean = -(-total // 256)
+    if groups < 8 and total > 16 * 32 * groups:
+        S = max(32, mean)
+    else:
+        S = max(8, mean * 65 // 100 if len(tiles) * per < 768 else mean)
+    assert plan.num_attn_splits == per * sum(t > S for t in tiles) > 0
+    # the ranges, not only what is split
+    assert plan.num_attn_items == mk(int(S)).num_attn_items
