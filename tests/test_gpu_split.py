@@ -26,9 +26,8 @@ def _local(name, **model_kw):
     return workloads.make_workload(cfg)
 
 
-def _check_all(run, expect_split=True):
-    if expect_split:
-        assert run.plan.num_attn_splits > 0, "no item was split"
+def _check_all(run):
+    assert run.plan.num_attn_splits > 0, "no item was split"
     assert run.pool_after_compose_ok and run.pool_after_attn_ok, "pool modified"
     for r in range(len(run.wl.requests)):
         check_request(run, r)
@@ -47,10 +46,7 @@ def test_split_local_matches_oracle(name, split, kernel):
     grouped by first visible key (3: a slot per row block and range)."""
     run = GpuRun(_local(name), split_tiles=split, attn_kernel=kernel)
     assert run.plan.attn_rows_per_item == (96 if kernel == 3 else 32)
-    # range boundaries stay at or below an item's smallest position: the
-    # small batch's grouped three-block items reach at most 4 tiles past it,
-    # so 5-tile ranges split none of them
-    _check_all(run, expect_split=not (kernel == 3 and split == 5))
+    _check_all(run)
 
 
 @pytest.mark.parametrize("G", [1, 2])
