@@ -76,7 +76,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // Waves of a workgroup: eight, and four at head_dim 256, where a wave's
-// output tile alone is 128 registers.
+// output tile alone is 128 registers (28 registers spill there, at one wave a
+// SIMD; three requests, 360 rows, 4 heads of 256: 4,059 us with the scalar
+// code, 204 so).
 template <int D> constexpr int kF32Waves = D == 256 ? 4 : 8;
 constexpr int kF32Rows = 16, kF32Keys = 16;
 
@@ -390,8 +392,7 @@ __global__ __launch_bounds__(256 * R, 3) void attn_mfma_kernel(
   // was split into scalars and copied right after the loads, which waits for
   // them before the tile's products (10-15 % slower).
   // K: direct loads; lane l fetches key l % 16, 8-dim chunk l / 16 of 32
-  //    dims, into its place in the fragment order (attn_common.h's order,
-  //    a 16-key block at a time).
+  //    dims, into its place in the fragment order (kKHalf).
   // V: lane l owns 16 bytes (dims 8 (l / 8) ..) of keys 2 (l % 8) and
   //    2 (l % 8) + 1, which sit next to each other in the permuted V^T row;
   //    each of its 8 dims takes one 4-byte write.

@@ -30,11 +30,12 @@ constexpr int kKT = 32;
 // the PV MFMA (4h .. 4h+3 and 8+4h .. 8+4h+3 for half-wave h, the order in
 // which the S^T accumulators hand out P^T) are one 16-byte LDS read.
 constexpr int kVStr = kKT + 8;         // fp16 elements per V^T row in LDS
-// A K tile sits in LDS in the order the QK^T MFMAs consume it: one 1 KB
-// block per 16-dim step kst, in which lane l's 16 bytes (at l * 16) are
-// K[l % 32][16 kst + 8 (l / 32) .. + 8].  Fragment reads are then
-// lane-contiguous (no bank conflicts, immediate offsets), and one direct
-// global->LDS load of 16 bytes per lane fills one block.
+// A K tile sits in LDS in 1 KB blocks in fragment order: a direct
+// global->LDS load of 16 bytes per lane fills one block, and fragment reads
+// are contiguous runs at immediate offsets (no bank conflicts).  In the
+// pipelined kernel a block is a 16-dim step kst of the QK^T MFMAs, lane l's 16
+// bytes (at l * 16) being K[l % 32][16 kst + 8 (l / 32) .. + 8]; the row-block
+// kernel's order is in attn.hip.
 constexpr int kKBlk = 1024;
 constexpr int kKBytes = 8 * kKBlk;
 constexpr int kVBytes = kD * kVStr * 2;
