@@ -492,10 +492,11 @@ tsr_status build_plan(const tsr_model* model, const tsr_request* reqs,
   std::vector<CombineDesc> combine[2];
   int32_t n_slots = 0, n_split_items = 0;
   // The automatic threshold (split_tiles == 0) applies to one-row-block
-  // plans only: on the LOCAL-scope RAG batch at three row blocks it split 64
-  // items and the launch plus merge took 4 % longer (one workgroup per
-  // compute unit there, so an item's tail is shared by fewer waiting
-  // items); split_tiles > 0 splits either.
+  // plans only: three-row-block plans keep no split buffer, so calls of one
+  // on concurrent streams share nothing.  (It would help some of them: 272
+  // items, 182 us whole and 156 in ranges of 56 to 80 tiles; the LOCAL-scope
+  // RAG batch took 4 % longer split, with an earlier merge kernel.)
+  // split_tiles > 0 splits either.
   const int rb_split = p->row_blocks;
   if ((split_tiles > 0 || (split_tiles == 0 && rb_split == 1)) &&
       (rb_split == 1 || rb_split == kMaxRowBlocks) &&
